@@ -51,6 +51,20 @@ struct TermItem {
   int32_t pad;
 };
 
+// One piece of a matrix-core term list: panel columns [c0, c1) of a leaf,
+// with everything of the leaf a workgroup needs to start on it, so that the
+// first panel loads wait on one load (of the item) and not on a chain.
+struct MMPiece {
+  int32_t leaf, m;           // leaf, its rows
+  int32_t c0, c1;            // panel columns
+  int32_t prow;              // first partial row of the piece
+  int32_t np, lp0;           // pieces of the leaf, its first entry in lprow
+  int32_t off;               // tree offset of the leaf
+  int64_t panel, col;        // element offset of the panel, first column in src
+  int64_t pad[2];
+};
+static_assert(sizeof(MMPiece) == 64, "one 64-byte item per piece");
+
 struct InRow {               // per-leaf W stacks of the in-row far blocks
   const void* W;             // double2 or float2 elements
   const int64_t* off;        // per leaf: complex-element offset of the stack
@@ -77,6 +91,8 @@ struct TermArgs {
   PanelSet ps;
   InRow ir;
   const TermItem* items;     // pieces, grouped by workgroup
+  const MMPiece* mpieces;    // the pieces of a matrix-core list
+  bool fp64_sums;            // FP32 blocks of this list: products and sums in FP64
   const int32_t* wptr;       // per workgroup: first piece (count + 1 entries)
   const int32_t* lptr;       // per leaf: first entry in lprow (nleaves + 1)
   const int32_t* lprow;      // partial rows of each leaf's pieces, fixed order
@@ -231,44 +247,43 @@ hipError_t launch_permute_out(const double2* in, int64_t ldi, const int64_t* per
                               int64_t ldx, int64_t n, int nrhs, hipStream_t st);
 // many-RHS variants on MFMA (FP32 3M, FP64 4M), inputs and partial sums
 // in row layout (TermArgs::xr / xr32, ldr), right-hand sides in tiles of
-// `tile` = 16/32/64 (0: by nrhs).  Leaves of at most kMmWaveLeaf rows run
-// one piece per wave (wave mode: nunits = waves, pieces grouped by wave);
-// larger leaves (up to 256 rows) one piece per workgroup, wave w taking
-// rows [w R, (w + 1) R) of the leaf, R = 32 or 64 (nunits = workgroups).
+// `tile` = 16/32/64 (0: by nrhs).  A unit of the list is the work of one
+// workgroup for one tile; cus: compute units of the device.
 hipError_t launch_term_mm(bool f32, int max_m, const TermArgs& a, int nunits, int nrhs, int tile,
-                          hipStream_t st);
-constexpr int kMmWaveLeaf = 64;
+                          int cus, hipStream_t st);
+constexpr int kMmSmallLeaf = 64;
+constexpr int kMmMaxCols = 2048;   // panel columns of a piece (their sources are staged in LDS)
+constexpr int kMmMinCols = 64;     // columns of a piece cut from a leaf, at least
 // zeroed bytes after every panel set the matrix-core kernels read (their row
 // tiles run up to 15 rows past a leaf's last column)
 constexpr size_t kPanelPad = 4096;
-inline bool mm_wave_mode(int max_m) { return max_m <= kMmWaveLeaf; }
+inline bool mm_small_leaf(int max_m) { return max_m <= kMmSmallLeaf; }
 // t rows of the listed group tiles (64 rows each) in row layout:
 // x[(N + t0 + q) ldr + c] = sum_j W_g[q, j] x[(s_off + j) ldr + c]
 hipError_t launch_stageA_mm(bool f32, const void* W, const Group* groups, const GroupItem* items,
                             int nitems, double2* xr, float2* xr32, int64_t ldr, int64_t N,
                             int zrow, int nrhs, int tile, hipStream_t st);
 // The K terms of the series on the matrix cores in one persistent launch
-// (wave mode: leaves of at most kMmWaveLeaf rows; one tile of at most 32
-// right-hand sides).  Work comes from a queue of wave items, term by term:
-// the stage-A tiles of every instance (64 rows of a group each), then the
-// term pieces of every instance.  Term k reads [y_{k-1} | t_k] from
+// (leaves of at most kMmSmallLeaf rows; one tile of at most 32
+// right-hand sides).  Work comes from a queue of items, one workgroup each,
+// term by term: the stage-A tiles of every instance (64 rows of a group
+// each), then the term pieces of every instance.  Term k reads [y_{k-1} | t_k] from
 // rows r[(k - 1) & 1] and its leaf epilogues write y_k to rows r[k & 1] and
 // x += y_k (TermArgs epilogue, alpha = -1).  Per (instance, term) two
 // counters count the stage-A tiles done and the leaf epilogues done; a
 // stage-A tile of term k starts once its instance's epilogues of term k - 1
 // are all done, a term piece once its instance's stage-A tiles of term k are
 // (and the epilogues of term k - 1).  Every wait is on items earlier in the
-// queue, each taken by a running wave, so every wait ends; a wait that gives
+// queue, each taken by a running workgroup, so every wait ends; a wait that gives
 // up sets *err.  Rows, x and the counters move through device-coherent
 // loads and stores (the terms of one leaf run on any XCD).  The queue and
-// the counters are zero between launches (the last wave out clears them).
+// the counters are zero between launches (the last workgroup out clears them).
 struct MMItem {
-  int32_t kind;              // 0: stage-A tile of group a; 1: term piece of leaf a
+  int32_t kind;              // 0: stage-A tile of group a; 1: term piece a
   int32_t inst;              // instance the item belongs to
-  int32_t a;
-  int32_t c0, c1;            // term piece: panel columns
-  int32_t prow;              // term piece: first partial row
+  int32_t a;                 // group, or index of the piece in its list
   int32_t row0, rows;        // stage-A tile: first row, active rows of the group
+  int32_t pad[3];
 };
 struct MMSeriesArgs {
   int K;
@@ -284,7 +299,7 @@ struct MMSeriesArgs {
   const int32_t* need_a;     // per instance: stage-A tiles of one term
   const int32_t* need_b;     // per instance: leaf epilogues of one term
   int ninst;
-  int32_t* queue;            // [next item, waves done]
+  int32_t* queue;            // [next item, workgroups done]
   int32_t* err;
   // outputs of the last term only (the TermArgs yout / out are ignored)
   double2* yout;

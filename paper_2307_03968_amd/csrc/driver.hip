@@ -44,6 +44,8 @@ void set_error(const std::string& msg) { g_err = msg; }
 
 struct TermList {
   TermItem* items = nullptr;   // device: pieces grouped by workgroup
+  MMPiece* mpieces = nullptr;  // device: the same for a matrix-core list
+  bool fp64_sums = false;      // matrix-core list: FP32 blocks are summed in FP64
   int32_t* wptr = nullptr;     // device: nwg + 1
   int32_t* lptr = nullptr;     // device: nleaves + 1
   int32_t* lprow = nullptr;    // device: partial rows of each leaf's pieces
@@ -52,7 +54,7 @@ struct TermList {
   int64_t rows = 0;            // partial rows
   int64_t vrow = 0;            // half lists: first partial row of the v slots
   int64_t frow = 0;            // half lists: first partial row of the far-pair slots
-  std::vector<TermItem> host;  // the pieces, in list order (before grouping)
+  std::vector<TermItem> host;  // the pieces, grouped by workgroup
 };
 
 struct GroupList {
@@ -191,10 +193,12 @@ struct hm_matrix {
   int mm_multi_mode = 2;        // 1: one launch for the K terms where it applies; 2: per term
   int mm_series_wgs[2][2] = {{0, 0}, {0, 0}};  // resident round by [f32][nrhs > 16]
   int mm_min_rhs = hm::kMmMinRhsDefault;  // right-hand sides from which the MFMA kernels run
+  bool mm_min_set = false;      // mm_min_rhs was chosen by the caller or the autotuner
   int rhs_tile = 0;             // MFMA right-hand-side tile (0: by nrhs)
   int inrow_pct = 100;          // cost weight (%) of in-row rows in the work split
   // per-leaf column layout of the panels, kept to rebuild the work lists
   std::vector<int64_t> near_cols, ir_cols;
+  std::vector<int64_t> R_off_h, R_col_h, M_off_h, M_col_h, Dinv_off_h;
   std::vector<int32_t> ir_ncol_h;
   std::vector<std::vector<int64_t>> ir_end, gl_end;
   std::vector<void*> list_allocs;  // device work lists (rebuilt by hmat_tune)
@@ -298,6 +302,33 @@ int level_index(const hm_matrix* h, int level, int* li) {
   return HM_OK;
 }
 
+// The panels a matrix-core list runs over: per leaf the panel's element
+// offset and its first column in the source list.
+struct MMPanels {
+  const std::vector<int64_t>* off;
+  const std::vector<int64_t>* col;
+  bool dinv;
+};
+
+// Units of work of the matrix-core term lists (one workgroup each, per tile
+// of right-hand sides) for a list of `total` entries.  Up to one unit per CU
+// while a unit keeps at least 16,384 entries (a piece pays its start, its sums
+// and its partial rows: cube 14^3, 7 M entries, 16 RHS, FP64: one unit per CU
+// 222 us a solve, two 250); two per CU, a resident round, from 48 M entries on
+// (sphere 24,576, 57 M, 16 RHS, FP64: 913 against 968), 64 M with small
+// leaves; for those eight from 200 M and sixteen from 800 M, so that the
+// dispatcher evens out units that take unequal time (64 instances, 247 M,
+// FP32: 547 us a term against 630 with two).  D^{-1} lists are small: a unit of 2,048 entries (a leaf of
+// 47 rows by itself; 16,384 took 84 us against 10 on 128 leaves).
+int64_t mm_two_per_cu(const hm_matrix* h) { return mm_small_leaf(h->max_m) ? 64000000 : 48000000; }
+int mm_units(const hm_matrix* h, int64_t total, bool dinv) {
+  const int64_t cus = h->num_cus;
+  int64_t u = std::min(total / (dinv ? 2048 : 16384), cus);
+  if (total >= mm_two_per_cu(h) || (dinv && total >= 2048 * cus)) u = 2 * cus;
+  if (!dinv && mm_small_leaf(h->max_m) && total >= 200000000) u = total >= 800000000 ? 16 * cus : 8 * cus;
+  return (int)std::max<int64_t>(8, u / 8 * 8);
+}
+
 // Pieces of one term kernel, split evenly over h->term_wgs persistent
 // workgroups.  Per leaf a, in order: dense column ranges dense[a] (pairs
 // [begin, end), cost m per column), then in-row stack rows [0, inrow_rows[a])
@@ -308,7 +339,7 @@ int level_index(const hm_matrix* h, int level, int* li) {
 int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t, int64_t>>>& dense,
                   const std::vector<int64_t>& inrow_rows, const std::vector<int64_t>& inrow_col,
                   const std::vector<int32_t>& inrow_ncol, TermList& tl, hipStream_t st,
-                  hm_matrix::HalfList* hl = nullptr, int units = 0, bool whole = false,
+                  hm_matrix::HalfList* hl = nullptr, const MMPanels* mm = nullptr,
                   const std::vector<int32_t>* npairs = nullptr) {
   struct Seg { int leaf, kind; int64_t u0, u1, col0, cost; };
   std::vector<Seg> segs;
@@ -332,10 +363,22 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     if (segs.size() == first) segs.push_back({a, 0, 0, 0, 0, 0});  // epilogue only
     for (size_t k = first; k < segs.size(); ++k) total += (segs[k].u1 - segs[k].u0) * segs[k].cost;
   }
-  // the half-storage kernel's own resident round unless a count was set
-  const int G = units > 0 ? units
-                          : std::max(1, hl && h->term_wgs == h->term_wgs_auto ? h->half_wgs_auto
-                                                                               : h->term_wgs);
+  // the half-storage kernel's own resident round and the matrix-core kernel's
+  // own unit count unless a count was set
+  const bool set = h->term_wgs != h->term_wgs_auto;
+  const int G = set ? h->term_wgs
+                    : (mm ? mm_units(h, total, mm->dinv) : std::max(1, hl ? h->half_wgs_auto : h->term_wgs));
+  // matrix-core pieces: FP32 blocks are summed in FP32 within a wave's part of
+  // a piece and in FP64 beyond it, with an error that grows with the root of
+  // the part's columns (about 1.5e-8 times it; series against FP64 blocks:
+  // sphere 24,576 4.0e-7, cube 32^3 9.4e-7).  Short lists (at most one unit
+  // per CU) take FP64 products instead (sphere 6,000, 64 RHS: 4.3e-8 in 450 us
+  // a solve; FP32 sums 1.8e-7 in 300); leaves whose waves do not split the
+  // columns keep their pieces at a 768th of the list.
+  const int64_t mm_cols =
+      h->max_m <= 96 ? kMmMaxCols
+                     : std::max<int64_t>(256, std::min<int64_t>(kMmMaxCols, total / (768 * h->max_m)));
+  tl.fp64_sums = mm && total < mm_two_per_cu(h);
   std::vector<TermItem> items;
   std::vector<int32_t> wg_of, vleaf, lcnt(hl ? h->nl : 0, 0);
   int64_t rows = 0, done = 0;
@@ -450,49 +493,32 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
   auto wg_at = [&](int64_t cost) {
     return total > 0 ? (int)std::min<int64_t>(G - 1, (cost * G) / total) : 0;
   };
-  if (whole && !hl) {
-    // whole leaves: every segment of a leaf is one piece of the same unit
-    // (no partial sums for a single-segment leaf); leaves go to the least
-    // loaded unit, largest first (LPT), and each unit runs its pieces in
-    // tree order
-    std::vector<int64_t> lcost(h->nl, 0);
-    for (const Seg& sg : segs) lcost[sg.leaf] += (sg.u1 - sg.u0) * sg.cost + 1;
-    std::vector<int> order(h->nl);
-    for (int a = 0; a < h->nl; ++a) order[a] = a;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return lcost[x] > lcost[y]; });
-    std::vector<std::pair<int64_t, int>> heap;  // (load, unit), min-heap
-    for (int g = 0; g < G; ++g) heap.push_back({0, g});
-    auto gt = [](const std::pair<int64_t, int>& x, const std::pair<int64_t, int>& y) { return x > y; };
-    std::make_heap(heap.begin(), heap.end(), gt);
-    std::vector<int> unit_of(h->nl, 0);
-    for (int a : order) {
-      std::pop_heap(heap.begin(), heap.end(), gt);
-      unit_of[a] = heap.back().second;
-      heap.back().first += lcost[a];
-      std::push_heap(heap.begin(), heap.end(), gt);
-    }
-    for (const Seg& sg : segs) {
-      const int m = h->H.leaf_size[sg.leaf];
-      TermItem it{sg.leaf, 0, (int32_t)sg.u0, (int32_t)sg.u1, 0, 0, (int32_t)rows, 0};
-      items.push_back(it);
-      wg_of.push_back(unit_of[sg.leaf]);
-      rows += m;
-    }
-  }
   // other lists: pieces split evenly over the G workgroups by cost, each
   // workgroup taking a contiguous run
-  for (size_t si = 0; si < (hl || whole ? 0 : segs.size()); ++si) {
+  for (size_t si = 0; si < (hl ? 0 : segs.size()); ++si) {
     const Seg& sg = segs[si];
     const int m = h->H.leaf_size[sg.leaf];
     int64_t u = sg.u0;
     do {
-      const int g = wg_at(done);
+      int g = wg_at(done);
       // units of this segment that start before the next workgroup boundary
       int64_t k = sg.u1 - u;
-      if (g < G - 1 && sg.cost > 0) {
+      auto to_bound = [&] {
+        if (g >= G - 1 || sg.cost <= 0) return;
         const int64_t bound = ((int64_t)(g + 1) * total + G - 1) / G;
-        k = std::min(k, std::max<int64_t>(1, (bound - done + sg.cost - 1) / sg.cost));
+        k = std::min(sg.u1 - u, std::max<int64_t>(1, (bound - done + sg.cost - 1) / sg.cost));
+      };
+      to_bound();
+      if (mm && k < sg.u1 - u) {
+        // no slivers: a piece pays its start and its sums however short it is
+        if (k < kMmMinCols && g < G - 1) {
+          ++g;
+          k = sg.u1 - u;
+          to_bound();
+        }
+        if (sg.u1 - u - k < kMmMinCols) k = sg.u1 - u;
       }
+      if (mm) k = std::min<int64_t>(k, mm_cols);
       if (sg.kind == 1) {
         // FP32 stacks are read two rows per load from an even row: keep
         // every in-row piece start even (kInRowTile is even)
@@ -575,8 +601,19 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
   tl.nwg = G;
   tl.npieces = (int)items.size();
   tl.rows = rows;
-  tl.host = items;
-  STCHK(upload(h, &tl.items, by_wg, st, true));
+  tl.host = by_wg;
+  if (mm) {
+    std::vector<MMPiece> mp;
+    mp.reserve(by_wg.size());
+    for (const TermItem& it : by_wg) {
+      const int a = it.leaf;
+      mp.push_back({a, h->H.leaf_size[a], it.c0, it.c1, it.prow, lptr[a + 1] - lptr[a], lptr[a],
+                    h->H.leaf_off[a], (*mm->off)[a], (*mm->col)[a], {0, 0}});
+    }
+    STCHK(upload(h, &tl.mpieces, mp, st, true));
+  } else {
+    STCHK(upload(h, &tl.items, by_wg, st, true));
+  }
   STCHK(upload(h, &tl.wptr, wptr, st, true));
   STCHK(upload(h, &tl.lptr, lptr, st, true));
   STCHK(upload(h, &tl.lprow, lprow, st, true));
@@ -688,6 +725,8 @@ TermArgs term_args(const hm_matrix* h, const PanelSet& ps, const TermList& tl, b
   t.ir = InRow{f32 ? (const void*)h->IR32 : (const void*)h->IR64, h->ir_off, h->ir_ld,
                h->ir_ncol, h->ir_row0, h->ir_soff, h->ir_n};
   t.items = tl.items;
+  t.mpieces = tl.mpieces;
+  t.fp64_sums = tl.fp64_sums;
   t.wptr = tl.wptr;
   t.lptr = tl.lptr;
   t.lprow = tl.lprow;
@@ -772,7 +811,13 @@ struct Path {
 Path pick_path(const hm_matrix* h, bool f32, int nrhs) {
   // the matrix-core kernels index the row-layout vectors with 32-bit offsets
   const bool fits = (h->N + h->T + 1) * row_ld(nrhs) * (int64_t)sizeof(double2) < ((int64_t)1 << 32);
-  if (nrhs >= h->mm_min_rhs && fits)
+  // FP64, threshold not chosen by the caller: the streaming kernels take four
+  // right-hand sides per panel read, so five to seven read it twice (cube 17^3,
+  // 7 RHS: 790 us a solve on them, 349 on the matrix cores; 4 RHS: 215 to 250
+  // on either).  FP32 blocks keep them up to the default threshold: they
+  // accumulate in FP64, the FP32 matrix cores do not.
+  const int min_rhs = h->mm_min_set || f32 ? h->mm_min_rhs : std::min(h->mm_min_rhs, kMmMinRhsF64);
+  if (nrhs >= min_rhs && fits)
     return Path{true, f32 ? (const void*)h->Wmm32 : (const void*)h->Wmm64, h->groups_mm,
                 &h->sa_mm, &h->tl_series_mm, &h->tl_apply_mm, h->src_mm};
   return Path{false, f32 ? (const void*)h->W32 : (const void*)h->W64, h->groups, &h->sa,
@@ -781,7 +826,7 @@ Path pick_path(const hm_matrix* h, bool f32, int nrhs) {
 
 hipError_t run_term(const hm_matrix* h, const Path& P, bool f32, const TermArgs& t,
                     const TermList& tl, int nrhs, hipStream_t st) {
-  return P.mm ? launch_term_mm(f32, h->max_m, t, tl.nwg, nrhs, h->rhs_tile, st)
+  return P.mm ? launch_term_mm(f32, h->max_m, t, tl.nwg, nrhs, h->rhs_tile, h->num_cus, st)
               : launch_term(f32, h->max_m, t, tl.nwg, nrhs, st);
 }
 
@@ -965,7 +1010,7 @@ int scaled_refine_pass(hm_matrix* h, int li, bool f32, int K, bool check, hipStr
 // whether the many-RHS series at level li runs as one multi-term launch
 bool mm_multi_ok(const hm_matrix* h, int li, int K, int nrhs) {
   return h->mm_multi_mode == 1 && h->mm_cnt && li < (int)h->mm_multi.size() && h->mm_multi[li].ok &&
-         K <= kMmSeriesMaxTerms && nrhs <= 32 && mm_wave_mode(h->max_m);
+         K <= kMmSeriesMaxTerms && nrhs <= 32 && mm_small_leaf(h->max_m);
 }
 
 int series_core(hm_matrix* h, int li, bool f32, int K, const double2* rhs, int64_t ldr,
@@ -1590,23 +1635,7 @@ bool check_arch(std::string* arch) {
   return std::strncmp(prop.gcnArchName, "gfx950", 6) == 0;
 }
 
-// Work units of the matrix-core term lists: waves when one wave takes a
-// whole leaf, else workgroups.
-int mm_units(const hm_matrix* h) {
-  return mm_wave_mode(h->max_m) ? 4 * h->term_wgs : h->term_wgs;
-}
-
-// One wave per whole leaf (no partial sums) when there are enough leaves
-// for the waves to even out: small leaves and at least two per unit.
-bool mm_whole(const hm_matrix* h) {
-  return mm_wave_mode(h->max_m) && h->nl >= 2 * mm_units(h);
-}
-
-// Term-kernel work lists for every level (one resident round of h->term_wgs
-// persistent workgroups): one-RHS lists (dense column ranges + in-row stack
-// rows), many-RHS lists (dense column ranges only: in-row U columns read t
-// like the global ones), and the D^{-1} list.  Replaces earlier lists.
-// Queue items of the multi-term matrix-core series at level li (wave mode):
+// Queue items of the multi-term matrix-core series at level li (small leaves):
 // the stage-A tiles (64 rows of a group each), then the term pieces of the
 // level's many-RHS series list; per instance the tiles and the leaves
 // (one epilogue each per term).
@@ -1617,15 +1646,16 @@ int build_mm_multi(hm_matrix* h, int li, hipStream_t st) {
   std::vector<int32_t> need_a(ninst, 0), need_b(ninst, 0);
   for (const GroupItem& gi : h->sa_mm_host[li]) {  // one item per 64-row tile of a group
     const int inst = h->group_mm_inst[gi.group];
-    items.push_back({0, inst, gi.group, 0, 0, 0, gi.row0, gi.rows});
+    items.push_back({0, inst, gi.group, gi.row0, gi.rows, {0, 0, 0}});
     need_a[inst]++;
   }
   const int n_a = (int)items.size();
   std::vector<char> seen(h->nl, 0);
-  for (const TermItem& it : h->tl_series_mm[li].host) {
+  for (int32_t q = 0; q < (int32_t)h->tl_series_mm[li].host.size(); ++q) {
+    const TermItem& it = h->tl_series_mm[li].host[q];
     if (it.kind != 0) return HM_OK;  // not a list this launch runs
     const int inst = H.leaf_inst[it.leaf];
-    items.push_back({1, inst, it.leaf, it.c0, it.c1, it.prow, 0, 0});
+    items.push_back({1, inst, q, 0, 0, {0, 0, 0}});
     if (!seen[it.leaf]) {
       seen[it.leaf] = 1;
       need_b[inst]++;
@@ -1649,6 +1679,10 @@ int build_mm_multi(hm_matrix* h, int li, hipStream_t st) {
   return HM_OK;
 }
 
+// Term-kernel work lists for every level (one resident round of h->term_wgs
+// persistent workgroups): one-RHS lists (dense column ranges + in-row stack
+// rows), many-RHS lists (dense column ranges only: in-row U columns read t
+// like the global ones), and the D^{-1} list.  Replaces earlier lists.
 int build_lists(hm_matrix* h, hipStream_t st) {
   HIPCHK(hipStreamSynchronize(st));
   for (void* p : h->list_allocs) (void)hipFree(p);
@@ -1666,6 +1700,8 @@ int build_lists(hm_matrix* h, hipStream_t st) {
   h->half.assign(h->half_ok ? h->nlev : 0, hm_matrix::HalfList());
   std::vector<std::vector<std::pair<int64_t, int64_t>>> dense(nl);
   std::vector<int64_t> irr(nl), irc(nl), zero(nl, 0);
+  const MMPanels pan_R{&h->R_off_h, &h->R_col_h, false}, pan_M{&h->M_off_h, &h->M_col_h, false},
+      pan_D{&h->Dinv_off_h, &h->R_col_h, true};
   for (int li = 0; li < h->nlev && h->half_ok; ++li) {
     // half storage: half-panel columns, the scaled far panels
     // [in-row U' | global U'] of the far blocks not stored as pairs, and
@@ -1677,8 +1713,8 @@ int build_lists(hm_matrix* h, hipStream_t st) {
       irr[a] = h->hir_end[li][a];
       irc[a] = 0;
     }
-    STCHK(make_termlist(h, dense, irr, irc, h->hir_ncol_h, h->half[li].tl, st, &h->half[li], 0,
-                        false, &h->fp_end[li]));
+    STCHK(make_termlist(h, dense, irr, irc, h->hir_ncol_h, h->half[li].tl, st, &h->half[li], nullptr,
+                        &h->fp_end[li]));
   }
   for (int li = 0; li < h->nlev; ++li) {
     for (int pass = 0; pass < 4; ++pass) {  // apply, series, apply MM, series MM
@@ -1696,7 +1732,7 @@ int build_lists(hm_matrix* h, hipStream_t st) {
       TermList& tl = mm ? (series ? h->tl_series_mm[li] : h->tl_apply_mm[li])
                         : (series ? h->tl_series[li] : h->tl_apply[li]);
       STCHK(make_termlist(h, dense, mm ? zero : irr, irc, h->ir_ncol_h, tl, st, nullptr,
-                          mm ? mm_units(h) : 0, mm && mm_whole(h)));
+                          mm ? (series ? &pan_M : &pan_R) : nullptr));
     }
   }
   for (int a = 0; a < nl; ++a) {
@@ -1704,8 +1740,7 @@ int build_lists(hm_matrix* h, hipStream_t st) {
     dense[a].push_back({0, H.leaf_size[a]});
   }
   STCHK(make_termlist(h, dense, zero, zero, h->ir_ncol_h, h->tl_dinv, st));
-  STCHK(make_termlist(h, dense, zero, zero, h->ir_ncol_h, h->tl_dinv_mm, st, nullptr, mm_units(h),
-                      true));
+  STCHK(make_termlist(h, dense, zero, zero, h->ir_ncol_h, h->tl_dinv_mm, st, nullptr, &pan_D));
   h->mm_multi.assign(h->nlev, hm_matrix::MMMulti());
   if (h->mm_cnt) {
     for (int li = 0; li < h->nlev; ++li) STCHK(build_mm_multi(h, li, st));
@@ -2698,6 +2733,11 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
 
   h->near_cols = near_cols;
   h->ir_cols = ir_cols;
+  h->R_off_h = R_off;
+  h->R_col_h = R_col;
+  h->M_off_h = M_off;
+  h->M_col_h = M_col;
+  h->Dinv_off_h = Dinv_off;
   h->ir_ncol_h = ir_ncol;
   h->ir_end = ir_end;
   h->gl_end = gl_end;
@@ -2833,7 +2873,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
     h->ncoef[li] = nc;
   }
   // counters and queue of the multi-term matrix-core launch (zero between launches)
-  if (mm_wave_mode(h->max_m)) {
+  if (mm_small_leaf(h->max_m)) {
     const int64_t ncnt = (int64_t)(h->inst_off.size() - 1) * kMmSeriesMaxTerms * 2 + 3;
     STCHK(dalloc(h, (void**)&h->mm_cnt, sizeof(int32_t) * ncnt));
     HIPCHK(hipMemsetAsync(h->mm_cnt, 0, sizeof(int32_t) * ncnt, st));
@@ -3501,6 +3541,7 @@ int hmat_tune(hm_matrix_t h, const hm_tuning* t, void* hip_stream) {
   }
   if (t->mm_min_rhs > 0) h->mm_min_rhs = t->mm_min_rhs;
   if (t->mm_min_rhs == -1) h->mm_min_rhs = kMmMinRhsDefault;
+  if (t->mm_min_rhs != 0) h->mm_min_set = t->mm_min_rhs > 0;
   if (t->rhs_tile > 0) h->rhs_tile = t->rhs_tile;
   if (t->rhs_tile == -1) h->rhs_tile = 0;
   int wgs = h->term_wgs;
@@ -3588,6 +3629,7 @@ int hmat_autotune(hm_matrix_t h, const ps_opts* opts, int32_t nrhs, void* hip_st
   // the matrix-core candidates with the K terms in one launch and per term
   const int multi0 = h->mm_multi_mode;
   hm_tuning bt{h->mm_min_rhs, h->term_wgs, h->rhs_tile, h->inrow_pct, halves[0], multi0};
+  h->mm_min_set = true;
   double bms = INFINITY;
   for (int w : wgs) {
     for (int pct : pcts) {
