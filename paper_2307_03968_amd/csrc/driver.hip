@@ -203,7 +203,9 @@ struct hm_matrix {
   std::vector<std::vector<int64_t>> ir_end, gl_end;
   std::vector<void*> list_allocs;  // device work lists (rebuilt by hmat_tune)
   int64_t list_bytes = 0;
-  int64_t partial_rows = 0;
+  int64_t partial_rows = 0;     // partial rows of the streaming lists, a column per right-hand side
+  int64_t partial_rows_half = 0;  // of the half lists (one right-hand side)
+  int64_t partial_rows_mm = 0;  // of the matrix-core lists, in row layout
   int term_wgs = 1024;          // persistent workgroups of a term kernel
   int term_wgs_auto = 1024;
   int num_cus = 256;            // compute units of the device
@@ -387,6 +389,19 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     // piece from a queue): pieces of bounded size, largest estimated cost
     // first so that the last pieces taken are small.
     std::vector<std::pair<int64_t, TermItem>> pcs;
+    // piece sizes by the size of the list: about 1,400 half-panel pieces of 96
+    // to kHalfPieceCols columns, and two to kHalfPiecePairs pairs.  Wide pieces
+    // cost the least per byte, but a short list then leaves workgroups idle
+    // and every term waits for its last piece (four terms, FP64, 256 columns
+    // and 8 pairs against this rule: sphere 1,536 132 -> 82 us a solve, 6,000
+    // 195 -> 149, 12,000 296 -> 265, 24,576 417 -> 408; cube 17^3 275 -> 218,
+    // 24^3 603 -> 600).
+    int64_t ncols = 0, npair = 0;
+    for (const Seg& sg : segs) (sg.kind == 2 ? ncols : npair) += sg.kind >= 2 ? sg.u1 - sg.u0 : 0;
+    const int64_t half_cols =
+        std::max<int64_t>(96, std::min<int64_t>(kHalfPieceCols, (ncols / 1400 + 31) / 32 * 32));
+    const int64_t half_pairs =
+        std::max<int64_t>(2, std::min<int64_t>(kHalfPiecePairs, (npair + 255) / 256));
     for (const Seg& sg : segs) {
       const int m = h->H.leaf_size[sg.leaf];
       int64_t u = sg.u0;
@@ -396,7 +411,7 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
         if (sg.kind == 0) k = std::min<int64_t>(k, kHalfChunk);
         std::vector<int32_t>::const_iterator b0, b1;
         if (sg.kind == 2) {
-          k = std::min<int64_t>(k, kHalfPieceCols);
+          k = std::min<int64_t>(k, half_cols);
           const std::vector<int32_t>& bc = h->hp_bcol[sg.leaf];
           b0 = std::upper_bound(bc.begin(), bc.end(), (int32_t)u) - 1;
           const int64_t nb = (int64_t)bc.size() - 1;
@@ -404,7 +419,7 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
           k = std::min<int64_t>(k, bc[lim] - u);
           b1 = std::upper_bound(bc.begin(), bc.end(), (int32_t)(u + k - 1));
         }
-        if (sg.kind == 3) k = std::min<int64_t>(k, kMaxVLeaves);
+        if (sg.kind == 3) k = std::min<int64_t>(k, half_pairs);
         TermItem it{sg.leaf, sg.kind, 0, 0, 0, 0, (int32_t)rows, 0};
         int64_t cost = k * sg.cost;
         if (sg.kind == 1) {
@@ -625,7 +640,8 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     STCHK(upload(h, &hl->lcnt, lcnt, st, true));
     STCHK(upload(h, &hl->vleaf, vleaf, st, true));
   }
-  h->partial_rows = std::max(h->partial_rows, rows);
+  int64_t& max_rows = mm ? h->partial_rows_mm : (hl ? h->partial_rows_half : h->partial_rows);
+  max_rows = std::max(max_rows, rows);
   return HM_OK;
 }
 
@@ -638,6 +654,13 @@ int upload_groups(hm_matrix* h, const std::vector<GroupItem>& v, GroupList& gl, 
 // kernels, per (leaf, block of rows < 4, 16-RHS tile) for the matrix cores.
 int64_t counter_count(const hm_matrix* h, int nrhs) {
   return (int64_t)h->nl * std::max<int64_t>(nrhs, 4 * ((nrhs + 15) / 16));
+}
+
+// Entries of the partial-sum buffer for nrhs right-hand sides: column layout
+// (streaming and, for one right-hand side, half-storage kernels) or row layout
+// (matrix cores).
+int64_t partial_entries(const hm_matrix* h, int nrhs) {
+  return std::max({h->partial_rows * nrhs, h->partial_rows_half, h->partial_rows_mm * row_ld(nrhs)});
 }
 
 __global__ void k_zero_i32(int32_t* __restrict__ p, int64_t n) {
@@ -692,7 +715,7 @@ int ensure_workspace(hm_matrix* h, int nrhs, hipStream_t st) {
   STCHK(al((void**)&h->bt, sizeof(double2) * h->N * nrhs));
   STCHK(al((void**)&h->rt, sizeof(double2) * h->N * nrhs));
   STCHK(al((void**)&h->dt, sizeof(double2) * h->N * nrhs));
-  STCHK(al((void**)&h->partial, sizeof(double2) * h->partial_rows * ldr));
+  STCHK(al((void**)&h->partial, sizeof(double2) * partial_entries(h, nrhs)));
   STCHK(al((void**)&h->nscratch, sizeof(double) * h->n_norm_items * nrhs * 2));
   STCHK(al((void**)&h->norms, sizeof(double) * h->nseg * nrhs * 2));
   STCHK(al((void**)&h->counters, sizeof(int32_t) * counter_count(h, nrhs)));
@@ -1689,8 +1712,8 @@ int build_lists(hm_matrix* h, hipStream_t st) {
   h->list_allocs.clear();
   h->bytes -= h->list_bytes;
   h->list_bytes = 0;
-  const int64_t old_rows = h->partial_rows;
-  h->partial_rows = 0;
+  const int64_t old_rows = h->partial_rows, old_half = h->partial_rows_half, old_mm = h->partial_rows_mm;
+  h->partial_rows = h->partial_rows_half = h->partial_rows_mm = 0;
   const HostH& H = h->H;
   const int nl = h->nl;
   h->tl_apply.assign(h->nlev, TermList());
@@ -1749,7 +1772,8 @@ int build_lists(hm_matrix* h, hipStream_t st) {
         h->mm_series_wgs[f][big] = h->num_cus * series_mm_occupancy(f != 0, big ? 32 : 16);
   }
   HIPCHK(hipStreamSynchronize(st));
-  if (h->partial_rows > old_rows) h->ws_nrhs = 0;  // workspace is sized by partial_rows
+  if (h->partial_rows > old_rows || h->partial_rows_half > old_half || h->partial_rows_mm > old_mm)
+    h->ws_nrhs = 0;  // the workspace is sized by the partial rows
   return HM_OK;
 }
 
@@ -3060,7 +3084,7 @@ int64_t carve_workspace(const hm_matrix* h, int nrhs, unsigned char* base, WsVie
   w.bt = (double2*)take(16 * h->N * nrhs);
   w.rt = (double2*)take(16 * h->N * nrhs);
   w.dt = (double2*)take(16 * h->N * nrhs);
-  w.partial = (double2*)take(16 * h->partial_rows * ldr);
+  w.partial = (double2*)take(16 * partial_entries(h, nrhs));
   w.counters = (int32_t*)take(4 * counter_count(h, nrhs));
   w.ldr = ldr;
   if (v) *v = w;
@@ -3833,12 +3857,20 @@ int64_t device_bytes_estimate(hm_matrix_t h, int nrhs) {
 // the device part is not built yet, else the handle's own).
 int64_t workspace_bytes(hm_matrix_t h, int nrhs, int64_t T) {
   if (h->device >= 0) T = h->T;
-  const int64_t partial = h->partial_rows > 0 ? h->partial_rows
-                                              : 2 * h->N + (int64_t)h->term_wgs * h->max_m;
-  const int64_t items = h->n_norm_items > 0 ? h->n_norm_items : h->N / kNormRows + 1;
   const int64_t ldr = row_ld(nrhs);
+  int64_t partial = partial_entries(h, nrhs);
+  if (h->partial_rows == 0) {
+    // not built yet: every piece of a list is a leaf's first or a unit's first
+    int64_t total = 0;
+    for (const NearBlock& nb : h->H.near)
+      total += (int64_t)h->H.leaf_size[nb.t_leaf] * h->H.leaf_size[nb.s_leaf];
+    for (const FarBlock& fb : h->H.far) total += (int64_t)h->H.lowrank[fb.src].r * fb.m;
+    partial = std::max(nrhs * (h->N + (int64_t)h->term_wgs * h->max_m),
+                       ldr * (h->N + (int64_t)mm_units(h, total, false) * h->max_m));
+  }
+  const int64_t items = h->n_norm_items > 0 ? h->n_norm_items : h->N / kNormRows + 1;
   return (int64_t)nrhs * (16 * 2 * (h->N + T) + 16 * 4 * h->N + 16 * (items + h->nseg)) +
-         ldr * (24 * 2 * (h->N + T) + 16 * partial) + 4 * counter_count(h, nrhs);
+         ldr * 24 * 2 * (h->N + T) + 16 * partial + 4 * counter_count(h, nrhs);
 }
 
 int workspace_rhs(hm_matrix_t h) { return h->ws_nrhs; }
