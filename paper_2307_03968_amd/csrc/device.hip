@@ -248,6 +248,74 @@ __global__ __launch_bounds__(kThreads) void k_stageA(const void* __restrict__ W,
   }
 }
 
+// The same for one right-hand side.  Bound by the reads of W_g.  Groups are
+// few (768 columns of some 139 rows at level 5 of the 24,576 sphere), so a
+// 128-row tile goes to four 32-row workgroups (two 64-row ones in FP32): half
+// a wave reads 512 consecutive bytes of a column, the eight halves take every
+// eighth column, 16 loads in flight each, and the inputs come from LDS.
+// Every far level of the 24,576 sphere, FP64: 75 us with one workgroup per
+// tile, 58 us so; the product 248 -> 237 us (quarter waves 243, 512 threads
+// with 8 loads each the same as this).
+constexpr int kStageAHalf = 32;  // lanes per column
+template <int E>
+__global__ __launch_bounds__(kThreads) void k_stageA_one(const void* __restrict__ W,
+                                                         const Group* __restrict__ groups,
+                                                         const GroupItem* __restrict__ items,
+                                                         double2* __restrict__ xin, int64_t N) {
+  using T = typename Elem<E>::T;
+  constexpr int ROWS = kStageAHalf * E, SUB = kGroupTile / ROWS;
+  constexpr int UNR = 16, STEP = kThreads / kStageAHalf, CH = 1024;
+  __shared__ double2 xs[CH];
+  __shared__ double2 red[STEP - 1][ROWS];
+  const GroupItem it = items[blockIdx.x / SUB];
+  const int row0 = it.row0 + (blockIdx.x % SUB) * ROWS;
+  if (row0 >= it.rows) return;
+  const Group g = groups[it.group];
+  const void* Wg = Elem<E>::offset(W, g.w_off);
+  const int hw = threadIdx.x / kStageAHalf, hl = threadIdx.x % kStageAHalf;
+  // lanes past the group's rows re-read its last ones (not stored)
+  const uint32_t ri = (uint32_t)min(row0 + hl * E, g.ld - E);
+  double2 acc[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc[e] = zero2();
+  for (int cb = 0; cb < g.n; cb += CH) {
+    const int nc = min(CH, g.n - cb);
+    __syncthreads();
+    for (int k = threadIdx.x; k < nc; k += kThreads) xs[k] = xin[g.s_off + cb + k];
+    __syncthreads();
+    for (int c = hw; c < nc; c += STEP * UNR) {
+      T a[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u)
+        a[u] = Elem<E>::load(Wg, ri + (uint32_t)(cb + min(c + STEP * u, nc - 1)) * (uint32_t)g.ld);
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const double2 x = c + STEP * u < nc ? xs[c + STEP * u] : zero2();
+#pragma unroll
+        for (int e = 0; e < E; ++e) cmac(acc[e], Elem<E>::get(a[u], e), x);
+      }
+    }
+  }
+  if (hw > 0) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) red[hw - 1][hl * E + e] = acc[e];
+  }
+  __syncthreads();
+  if (hw == 0) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int row = row0 + hl * E + e;
+      double2 z = acc[e];
+#pragma unroll
+      for (int k = 0; k < STEP - 1; ++k) {
+        z.x += red[k][hl * E + e].x;
+        z.y += red[k][hl * E + e].y;
+      }
+      if (row < it.rows) xin[N + g.t0 + row] = z;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- leaf LU
 // Right-looking LU with partial pivoting of one leaf self-block per
 // workgroup, in place (column-major, ld = m).  Build-time only.
@@ -630,8 +698,8 @@ static hipError_t stageA_e(const void* W, const Group* groups, const GroupItem* 
   const int nr = pick_nr(nrhs);
   const dim3 grid(nitems, (nrhs + nr - 1) / nr);
   if (nr == 1)
-    hipLaunchKernelGGL((k_stageA<E, G, 1, 4>), grid, dim3(kThreads), 0, st, W, groups, items,
-                       xin, ldx, N, nrhs);
+    hipLaunchKernelGGL((k_stageA_one<E>), dim3(nitems * (kGroupTile / (kStageAHalf * E))),
+                       dim3(kThreads), 0, st, W, groups, items, xin, N);
   else if (nr == 2)
     hipLaunchKernelGGL((k_stageA<E, G, 2, 2>), grid, dim3(kThreads), 0, st, W, groups, items,
                        xin, ldx, N, nrhs);
