@@ -589,7 +589,10 @@ __global__ __launch_bounds__(kThreads) void k_half(HalfArgs A, MultiArgs M) {
 #pragma unroll
           for (int g = 0; g < GW; ++g)
 #pragma unroll
-            for (int e = 0; e < E; ++e) tbuf[(g * 64 + lane) * E + e] = tacc[g][e][0];
+            for (int e = 0; e < E; ++e) {
+              const int i = (g * 64 + lane) * E + e;
+              tbuf[i] = i >= it.pad ? tacc[g][e][0] : zero2();
+            }
         }
         __syncthreads();
         auto X = [&](int c, int) -> double2 { return tbuf[c - it.c0]; };

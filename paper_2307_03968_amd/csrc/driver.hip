@@ -239,6 +239,15 @@ struct hm_matrix {
   // nested multi-level solve: a LIFO pool of N x nrhs work vectors
   double2* nest_pool = nullptr;
   int nest_cap = 0, nest_nrhs = 0;
+  // half lists of the far blocks of exactly one level and their stage-A tiles
+  // (nested solves; made by the first one that needs the level)
+  struct LevelList {
+    bool built = false;
+    HalfList hl;
+    hm::GroupList sa;
+  };
+  std::vector<LevelList> nest_half;
+  std::vector<std::vector<int32_t>> sa_rows_h;  // per one-RHS group and level: rows (as its tiles)
   // per-kernel timing
   bool prof = false;
   struct ProfRec { int cls; hipEvent_t e0, e1; };
@@ -331,6 +340,13 @@ int mm_units(const hm_matrix* h, int64_t total, bool dinv) {
   return (int)std::max<int64_t>(8, u / 8 * 8);
 }
 
+// First far blocks of a half list that holds those of one level only (and no
+// half-panel columns): in-row stack rows and far pairs per leaf.
+struct FarFirst {
+  const std::vector<int64_t>* rows;
+  const std::vector<int32_t>* pairs;
+};
+
 // Pieces of one term kernel, split evenly over h->term_wgs persistent
 // workgroups.  Per leaf a, in order: dense column ranges dense[a] (pairs
 // [begin, end), cost m per column), then in-row stack rows [0, inrow_rows[a])
@@ -342,25 +358,27 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
                   const std::vector<int64_t>& inrow_rows, const std::vector<int64_t>& inrow_col,
                   const std::vector<int32_t>& inrow_ncol, TermList& tl, hipStream_t st,
                   hm_matrix::HalfList* hl = nullptr, const MMPanels* mm = nullptr,
-                  const std::vector<int32_t>* npairs = nullptr) {
+                  const std::vector<int32_t>* npairs = nullptr, const FarFirst* ff = nullptr) {
   struct Seg { int leaf, kind; int64_t u0, u1, col0, cost; };
   std::vector<Seg> segs;
   int64_t total = 0;
   for (int a = 0; a < h->nl; ++a) {
     const int64_t m = h->H.leaf_size[a];
     const size_t first = segs.size();
-    if (hl && h->hp_ncol[a] > 0) segs.push_back({a, 2, 0, h->hp_ncol[a], 0, m * h->half_pct / 100});
+    if (hl && !ff && h->hp_ncol[a] > 0) segs.push_back({a, 2, 0, h->hp_ncol[a], 0, m * h->half_pct / 100});
     for (auto& r : dense[a])
       if (r.second > r.first) segs.push_back({a, 0, r.first, r.second, 0, m});
-    if (inrow_rows[a] > 0)
-      segs.push_back({a, 1, 0, inrow_rows[a], inrow_col[a],
+    const int64_t row_a = ff ? (*ff->rows)[a] : 0;
+    if (inrow_rows[a] > row_a)
+      segs.push_back({a, 1, row_a, inrow_rows[a], inrow_col[a],
                       ((int64_t)inrow_ncol[a] + m) * h->inrow_pct / 100});
-    if (hl && npairs && (*npairs)[a] > 0) {  // far pairs: cost of the leaf's average pair
+    const int32_t pair_a = ff ? (*ff->pairs)[a] : 0;
+    if (hl && npairs && (*npairs)[a] > pair_a) {  // far pairs: cost of the leaf's average pair
       const int32_t p0 = h->fp_first_h[a], np = (*npairs)[a];
       int64_t c = 0;
-      for (int32_t p = p0; p < p0 + np; ++p)
+      for (int32_t p = p0 + pair_a; p < p0 + np; ++p)
         c += (int64_t)h->fp_rank_h[p] * (m + h->H.leaf_size[h->fp_tgt_h[p]]);
-      segs.push_back({a, 3, 0, np, 0, std::max<int64_t>(1, c / np)});
+      segs.push_back({a, 3, pair_a, np, 0, std::max<int64_t>(1, c / (np - pair_a))});
     }
     if (segs.size() == first) segs.push_back({a, 0, 0, 0, 0, 0});  // epilogue only
     for (size_t k = first; k < segs.size(); ++k) total += (segs[k].u1 - segs[k].u0) * segs[k].cost;
@@ -407,7 +425,7 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
       int64_t u = sg.u0;
       do {
         int64_t k = sg.u1 - u;
-        if (sg.kind == 1) k = std::min<int64_t>(k, kHalfInRowTile);  // starts stay even
+        if (sg.kind == 1) k = std::min<int64_t>(k, kHalfInRowTile - (u & 1));
         if (sg.kind == 0) k = std::min<int64_t>(k, kHalfChunk);
         std::vector<int32_t>::const_iterator b0, b1;
         if (sg.kind == 2) {
@@ -423,9 +441,12 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
         TermItem it{sg.leaf, sg.kind, 0, 0, 0, 0, (int32_t)rows, 0};
         int64_t cost = k * sg.cost;
         if (sg.kind == 1) {
-          it.r0 = (int32_t)u;
+          // FP32 stacks are read two rows per load: a piece starts at an even
+          // row, and one that begins in between counts that row as zero (pad)
+          it.pad = (int32_t)(u & 1);
+          it.r0 = (int32_t)u - it.pad;
           it.r1 = (int32_t)(u + k);
-          it.c0 = (int32_t)(sg.col0 + u);
+          it.c0 = (int32_t)sg.col0 + it.r0;
           it.c1 = (int32_t)(sg.col0 + u + k);
         } else if (sg.kind == 3) {
           it.c0 = (int32_t)(h->fp_first_h[sg.leaf] + u);
@@ -588,7 +609,7 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
   if (hl)
     for (int a = 0; a < h->nl; ++a) {
       std::sort(pair_in[a].begin(), pair_in[a].end());
-      lptr[a + 1] += h->vptr_h[a + 1] - h->vptr_h[a] + (int32_t)pair_in[a].size();
+      lptr[a + 1] += (ff ? 0 : h->vptr_h[a + 1] - h->vptr_h[a]) + (int32_t)pair_in[a].size();
     }
   for (int a = 0; a < h->nl; ++a) lptr[a + 1] += lptr[a];
   lprow.assign(lptr[h->nl], 0);
@@ -600,10 +621,10 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     return HM_EINVAL;
   }
   if (hl) {
-    for (int a = 0; a < h->nl; ++a)
+    for (int a = 0; a < h->nl && !ff; ++a)
       for (int q = h->vptr_h[a]; q < h->vptr_h[a + 1]; ++q)
         lprow[lf[a]++] = (int32_t)(rows + h->vstart_h[q]);
-    rows += h->hp_cols;
+    if (!ff) rows += h->hp_cols;
     tl.frow = rows;
     if (rows + h->fp_rows >= ((int64_t)1 << 31)) {
       set_error("term partial rows exceed 2^31");
@@ -871,8 +892,8 @@ bool use_half(const hm_matrix* h, int li, int nrhs) {
 }
 
 // One scaled term product at level li: input yhat = [y | t] (tree order).
-HalfArgs half_args(const hm_matrix* h, int li, bool f32, const double2* xin, int64_t ldx) {
-  const hm_matrix::HalfList& L = h->half[li];
+HalfArgs half_args(const hm_matrix* h, const hm_matrix::HalfList& L, bool f32, const double2* xin,
+                   int64_t ldx) {
   HalfArgs a{};
   a.t = term_args(h, PanelSet{f32 ? (const void*)h->HF32 : (const void*)h->HF64, h->hf_off, h->src,
                               h->hf_col, h->leaf_m},
@@ -941,7 +962,7 @@ int scaled_terms(hm_matrix* h, int li, bool f32, int K, double2* xh, double2** l
   double2* y_nxt = h->xin1;
   if (K > 0 && h->use_half == 1 && h->half[li].multi) {
     // all K terms in one launch (pieces gated by per-leaf term marks)
-    HalfArgs ha = half_args(h, li, f32, y_cur, ldin);
+    HalfArgs ha = half_args(h, h->half[li], f32, y_cur, ldin);
     ha.t.alpha = -1.0;
     const MultiArgs m{K, h->nl, {y_cur, y_nxt}, xh, h->hdone, h->herr};
     // a resident round of the multi-term kernel (pieces come from its queue,
@@ -956,7 +977,7 @@ int scaled_terms(hm_matrix* h, int li, bool f32, int K, double2* xh, double2** l
   for (int k = 1; k <= K; ++k) {
     if (sa1.n > 0)
       TIMED(HM_K_STAGEA, launch_stageA(f32, W1, h->groups, sa1.items, sa1.n, y_cur, ldin, N, 1, st));
-    HalfArgs ha = half_args(h, li, f32, y_cur, ldin);
+    HalfArgs ha = half_args(h, h->half[li], f32, y_cur, ldin);
     ha.t.alpha = -1.0;
     ha.t.yout = y_nxt;
     ha.t.ldy = ldin;
@@ -1007,7 +1028,7 @@ int scaled_refine_pass(hm_matrix* h, int li, bool f32, int K, bool check, hipStr
   const GroupList& sa1 = h->sa[li];
   if (sa1.n > 0)
     TIMED(HM_K_STAGEA, launch_stageA(false, h->WT64, h->groups, sa1.items, sa1.n, h->xin1, ldin, N, 1, st));
-  HalfArgs ha = half_args(h, li, false, h->xin1, ldin);
+  HalfArgs ha = half_args(h, h->half[li], false, h->xin1, ldin);
   ha.t.alpha = -1.0;
   ha.t.beta = 1.0;
   ha.t.v = h->bt;
@@ -1206,7 +1227,7 @@ int apply_core(hm_matrix* h, int li, bool f32, int nrhs, double alpha, double be
     if (sa1.n > 0)
       TIMED(HM_K_STAGEA, launch_stageA(f32, f32 ? (const void*)h->WT32 : (const void*)h->WT64,
                                        h->groups, sa1.items, sa1.n, h->xin1, ldin, N, 1, st));
-    HalfArgs ha = half_args(h, li, f32, h->xin1, ldin);
+    HalfArgs ha = half_args(h, h->half[li], f32, h->xin1, ldin);
     ha.t.alpha = 1.0;
     ha.t.beta = 1.0;
     ha.t.v = h->xin1;
@@ -1347,7 +1368,7 @@ int gmres_solve(hm_matrix* h, int li, bool f32, int K, int m, int max_iter, doub
     HIPCHK(launch_axpy(1.0, in, N, h->xin1, ldin, N, 1, 0, st));
     if (sa1.n > 0)
       TIMED(HM_K_STAGEA, launch_stageA(false, h->WT64, h->groups, sa1.items, sa1.n, h->xin1, ldin, N, 1, st));
-    HalfArgs ha = half_args(h, li, false, h->xin1, ldin);
+    HalfArgs ha = half_args(h, h->half[li], false, h->xin1, ldin);
     ha.t.alpha = alpha;
     ha.t.beta = beta;
     ha.t.v = v;
@@ -1537,6 +1558,34 @@ hipError_t dinv_pass(hm_matrix* h, const double2* in, const double2* v, double b
   return run_term(h, P, false, t, tl, nrhs, st);
 }
 
+// The far blocks of exactly level li (not the leaf level's) as a half list: the
+// blocks between the ends of the next finer level and its own.
+int build_level_list(hm_matrix* h, int li, hipStream_t st) {
+  hm_matrix::LevelList& LL = h->nest_half[li];
+  if (LL.built) return HM_OK;
+  const int fine = li + 1;
+  std::vector<std::vector<std::pair<int64_t, int64_t>>> dense(h->nl);
+  std::vector<int64_t> irc(h->nl, 0);
+  for (int a = 0; a < h->nl; ++a) {
+    const int64_t gstart = h->hir_cols[a];
+    if (h->gl_end[li][a] > h->gl_end[fine][a])
+      dense[a].push_back({gstart + h->gl_end[fine][a], gstart + h->gl_end[li][a]});
+  }
+  const FarFirst ff{&h->hir_end[fine], &h->fp_end[fine]};
+  STCHK(make_termlist(h, dense, h->hir_end[li], irc, h->hir_ncol_h, LL.hl.tl, st, &LL.hl, nullptr,
+                      &h->fp_end[li], &ff));
+  std::vector<GroupItem> items;
+  for (int32_t g = 0; g < (int32_t)h->sa_rows_h.size(); ++g) {
+    const int32_t r1 = h->sa_rows_h[g][li];  // from an even row (FP32 loads take two)
+    for (int32_t r0 = h->sa_rows_h[g][fine] & ~1; h->sa_rows_h[g][fine] < r1 && r0 < r1; r0 += kGroupTile)
+      items.push_back({g, r0, r1, 0});
+  }
+  LL.sa.n = (int)items.size();
+  STCHK(upload(h, &LL.sa.items, items, st, true));
+  LL.built = true;
+  return HM_OK;
+}
+
 constexpr int64_t kMaxNestedProducts = 100000;  // level products per nested solve, at most
 
 // The nested multi-level form of eq. 14-22 with factors from the leaf level
@@ -1600,6 +1649,66 @@ struct Nested {
   }
 };
 
+// The same for one right-hand side in the scaled basis of the half storage
+// (xhat = C^T x, S = C^{-1} R C^{-T}): U_1 is S at the leaf level, U_j the
+// scaled far blocks of one level (their own list), so a product is one launch
+// over that part of S, the leaf-level factor is one multi-term launch, and no
+// product, block-diagonal or difference pass stands between them.  24,576
+// sphere, levels 8 and 7, K = 4, FP64: 4,340 us with U_j from the difference of
+// two level products and D^{-1}, 2,190 us so.
+struct NestedHalf {
+  hm_matrix* h;
+  bool f32;
+  int K;
+  hipStream_t st;
+  const std::vector<int>& lev;  // level of each factor (index 0: the leaf level)
+  int top = 0;
+  double2* get() { return h->nest_pool + (int64_t)(top++) * h->N; }
+  void put() { --top; }
+  int li(int l) const { return h->lmin < 0 ? 0 : l - h->lmin; }
+  // v <- S_{j-1}(... S_0(v)); xin0 holds v too
+  int Q(int j, double2* v) {
+    for (int i = 0; i < j; ++i) STCHK(S(i, v));
+    return HM_OK;
+  }
+  // u <- sum_{k<=K} (-X_i)^k u; for i = 0 xin0 holds u too
+  int S(int i, double2* u) {
+    const int64_t N = h->N, ldin = h->N + h->T;
+    if (K == 0) return HM_OK;
+    if (i == 0) {
+      double2* last = nullptr;
+      return scaled_terms(h, li(lev[0]), f32, K, u, &last, st);
+    }
+    const hm_matrix::LevelList& LL = h->nest_half[li(lev[i])];
+    double2* y = get();
+    double2* w = get();
+    const double2* in = u;
+    for (int k = 1; k <= K; ++k) {
+      if (LL.sa.n > 0) {  // [y | t]
+        HIPCHK(launch_axpy(1.0, in, N, h->xin1, ldin, N, 1, 0, st));
+        TIMED(HM_K_STAGEA, launch_stageA(f32, f32 ? (const void*)h->WT32 : (const void*)h->WT64,
+                                         h->groups, LL.sa.items, LL.sa.n, h->xin1, ldin, N, 1, st));
+        in = h->xin1;
+      }
+      HalfArgs ha = half_args(h, LL.hl, f32, in, ldin);
+      ha.t.alpha = -1.0;
+      ha.t.yout = h->xin0;
+      ha.t.ldy = ldin;
+      ha.t.xacc = w;
+      ha.t.ldxa = N;
+      ha.t.accumulate = 0;
+      TIMED(HM_K_TERM_APPLY, launch_half(f32, h->max_m, ha, LL.hl.tl.nwg, st));
+      STCHK(Q(i, w));  // -X_i y
+      HIPCHK(launch_axpy(1.0, w, N, u, N, N, 1, 1, st));
+      std::swap(y, w);
+      in = y;
+    }
+    put();
+    put();
+    return HM_OK;
+  }
+};
+
 int nested_solve(hm_matrix* h, int level, bool f32, int K, const double2* b_dev, int64_t ldb,
                  double2* x_dev, int64_t ldx, int nrhs, hipStream_t st) {
   Nested ns{h, f32, K, nrhs, st};
@@ -1639,6 +1748,31 @@ int nested_solve(hm_matrix* h, int level, bool f32, int K, const double2* b_dev,
     }
     h->nest_cap = ncap;
     h->nest_nrhs = nr;
+  }
+  if (use_half(h, 0, nrhs)) {
+    bool lists = true;
+    const int64_t rows = h->partial_rows_half;
+    for (int j = 1; j < n && lists; ++j) {
+      const int li = ns.li(ns.lev[j]);
+      if (h->nest_half[li].built) continue;
+      // made outside a capture; a capture without them takes the general form
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+      HIPCHK(hipStreamIsCapturing(st, &cs));
+      lists = cs == hipStreamCaptureStatusNone;
+      if (lists) STCHK(build_level_list(h, li, st));
+    }
+    if (h->partial_rows_half > rows) {  // the workspace is sized by the partial rows
+      h->ws_nrhs = 0;
+      STCHK(ensure_workspace(h, nrhs, st));
+    }
+    if (lists) {
+      NestedHalf nh{h, f32, K, st, ns.lev};
+      double2* x = nh.get();
+      HIPCHK(block_pass(h, chat_set(h, false), b_dev, ldb, true, h->xin0, ns.ldin, x, 0, nullptr, 0, st));
+      STCHK(nh.Q(n, x));
+      HIPCHK(block_pass(h, chat_set(h, true), x, h->N, false, nullptr, 0, nullptr, 0, x_dev, ldx, st));
+      return HM_OK;
+    }
   }
   double2* x = ns.get();
   HIPCHK(launch_permute_in(b_dev, ldb, h->perm, h->bt, h->N, h->N, nrhs, st));
@@ -1721,6 +1855,8 @@ int build_lists(hm_matrix* h, hipStream_t st) {
   h->tl_apply_mm.assign(h->nlev, TermList());
   h->tl_series_mm.assign(h->nlev, TermList());
   h->half.assign(h->half_ok ? h->nlev : 0, hm_matrix::HalfList());
+  std::vector<hm_matrix::LevelList> old_nest(h->nlev);
+  old_nest.swap(h->nest_half);
   std::vector<std::vector<std::pair<int64_t, int64_t>>> dense(nl);
   std::vector<int64_t> irr(nl), irc(nl), zero(nl, 0);
   const MMPanels pan_R{&h->R_off_h, &h->R_col_h, false}, pan_M{&h->M_off_h, &h->M_col_h, false},
@@ -1739,6 +1875,8 @@ int build_lists(hm_matrix* h, hipStream_t st) {
     STCHK(make_termlist(h, dense, irr, irc, h->hir_ncol_h, h->half[li].tl, st, &h->half[li], nullptr,
                         &h->fp_end[li]));
   }
+  for (int li = 0; li < (int)old_nest.size() && h->half_ok; ++li)  // those in use before
+    if (old_nest[li].built) STCHK(build_level_list(h, li, st));
   for (int li = 0; li < h->nlev; ++li) {
     for (int pass = 0; pass < 4; ++pass) {  // apply, series, apply MM, series MM
       const bool series = pass & 1, mm = pass >= 2;
@@ -2862,6 +3000,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   h->sa.assign(h->nlev, GroupList());
   h->sa_mm.assign(h->nlev, GroupList());
   h->sa_mm_host.assign(h->nlev, std::vector<GroupItem>());
+  h->sa_rows_h = gs1.rows;
   h->group_mm_inst.assign(gsm.groups.size(), 0);
   for (size_t g = 0; g < gsm.groups.size(); ++g)
     h->group_mm_inst[g] = H.leaf_inst[H.tree.leaf_of[gsm.groups[g].s_off]];
