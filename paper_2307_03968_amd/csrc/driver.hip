@@ -1356,7 +1356,8 @@ int gmres_solve(hm_matrix* h, int li, bool f32, int K, int m, int max_iter, doub
   double2* V = h->gm_V;
   double2* Zb = h->gm_Z;
   double* hres = h->gm_host;               // nrhs residuals
-  double* hact = h->gm_host + nrhs;         // nrhs flags (as doubles)
+  S.host_resid = h->gm_host;
+  S.host_act = reinterpret_cast<int32_t*>(h->gm_host + nrhs);
   const bool scaled = use_half(h, li, nrhs) && h->nseg == 1;
   const GroupList& sa1 = h->sa[li];
   auto dots = [&](const double2* Vb, int nvec, const double2* w, double2* out, int ldo) {
@@ -1365,10 +1366,11 @@ int gmres_solve(hm_matrix* h, int li, bool f32, int K, int m, int max_iter, doub
   // scaled basis: out = alpha S in + beta v (FP64 half-storage product)
   auto s_apply = [&](const double2* in, double alpha, double beta, const double2* v,
                      double2* out) -> int {
-    HIPCHK(launch_axpy(1.0, in, N, h->xin1, ldin, N, 1, 0, st));
-    if (sa1.n > 0)
+    if (sa1.n > 0) {  // [in | t]
+      HIPCHK(launch_axpy(1.0, in, N, h->xin1, ldin, N, 1, 0, st));
       TIMED(HM_K_STAGEA, launch_stageA(false, h->WT64, h->groups, sa1.items, sa1.n, h->xin1, ldin, N, 1, st));
-    HalfArgs ha = half_args(h, h->half[li], false, h->xin1, ldin);
+    }
+    HalfArgs ha = half_args(h, h->half[li], false, sa1.n > 0 ? h->xin1 : in, ldin);
     ha.t.alpha = alpha;
     ha.t.beta = beta;
     ha.t.v = v;
@@ -1379,11 +1381,9 @@ int gmres_solve(hm_matrix* h, int li, bool f32, int K, int m, int max_iter, doub
     TIMED(HM_K_TERM_APPLY, launch_half(false, h->max_m, ha, h->half[li].tl.nwg, st));
     return HM_OK;
   };
-  // z = P v
+  // z = P v (scaled basis: xin0 and z hold v already)
   auto precond = [&](const double2* v, double2* z) -> int {
     if (!scaled) return series_core(h, li, f32, K, v, N, false, z, nullptr, 0, nrhs, false, st);
-    HIPCHK(launch_axpy(1.0, v, N, h->xin0, ldin, N, 1, 0, st));
-    HIPCHK(launch_axpy(1.0, v, N, z, N, N, 1, 0, st));
     double2* last = nullptr;
     return scaled_terms(h, li, f32, K, z, &last, st);
   };
@@ -1398,17 +1398,10 @@ int gmres_solve(hm_matrix* h, int li, bool f32, int K, int m, int max_iter, doub
   std::vector<int> active(nrhs, 0);
   std::vector<double> rel_true(nrhs, 1.0);
   double bn_true = 0.0;
-  auto read_state = [&](bool flags) -> int {
-    HIPCHK(hipMemcpyAsync(hres, S.resid, sizeof(double) * nrhs, hipMemcpyDeviceToHost, st));
-    if (flags) {
-      // the int flags land in the second half of the pinned buffer
-      HIPCHK(hipMemcpyAsync(hact, S.act, sizeof(int32_t) * nrhs, hipMemcpyDeviceToHost, st));
-    }
+  // residual estimates and flags, once the stream's last kstart or kstep is done
+  auto read_state = [&]() -> int {
     HIPCHK(hipStreamSynchronize(st));
-    if (flags) {
-      const int32_t* f = reinterpret_cast<const int32_t*>(hact);
-      for (int c = 0; c < nrhs; ++c) active[c] = f[c];
-    }
+    for (int c = 0; c < nrhs; ++c) active[c] = S.host_act[c];
     return HM_OK;
   };
   // ||v||^2 of the single column of v, read to the host
@@ -1471,8 +1464,8 @@ int gmres_solve(hm_matrix* h, int li, bool f32, int K, int m, int max_iter, doub
     // V_0 holds the residual r: ||r||, g = ||r|| e_1, V_0 = r / ||r||
     HIPCHK(dots(V, 1, V, h->gm_hn, 1));
     HIPCHK(launch_kstart(S, h->gm_hn, h->gm_bn, tol_s, nrhs, st));
-    HIPCHK(launch_kscale(V, N, S.inv, N, nrhs, st));
-    STCHK(read_state(true));
+    HIPCHK(launch_kscale(V, N, S.inv, N, nrhs, scaled ? h->xin0 : nullptr, scaled ? Zb : nullptr, st));
+    STCHK(read_state());
     if (!scaled)
       for (int c = 0; c < nrhs; ++c) rel[c] = hres[c];
     bool any = false;
@@ -1494,15 +1487,14 @@ int gmres_solve(hm_matrix* h, int li, bool f32, int K, int m, int max_iter, doub
       STCHK(oper(zj, w));
       // two classical Gram-Schmidt passes against v_0 .. v_j
       HIPCHK(dots(V, j + 1, w, h->gm_h1, m + 1));
-      HIPCHK(launch_kupdate(-1.0, V, vs, N, h->gm_h1, m + 1, j + 1, w, N, nrhs, st));
-      HIPCHK(dots(V, j + 1, w, h->gm_h2, m + 1));
-      HIPCHK(launch_kupdate(-1.0, V, vs, N, h->gm_h2, m + 1, j + 1, w, N, nrhs, st));
-      HIPCHK(dots(w, 1, w, h->gm_hn, 1));
-      HIPCHK(launch_kstep(S, j, h->gm_h1, h->gm_h2, m + 1, h->gm_hn, tol_s, nrhs, st));
-      HIPCHK(launch_kscale(w, N, S.inv, N, nrhs, st));
+      HIPCHK(launch_korth(V, vs, N, h->gm_h1, h->gm_h2, m + 1, j + 1, w, N, nrhs, h->gm_part, st));
+      HIPCHK(launch_kstep(S, j, h->gm_h1, h->gm_h2, m + 1, h->gm_part, N, tol_s, nrhs, st));
+      // v_{j+1}; scaled basis: also where the next step's series starts
+      const bool next = scaled && j + 1 < m;
+      HIPCHK(launch_kscale(w, N, S.inv, N, nrhs, next ? h->xin0 : nullptr, next ? zj + vs : nullptr, st));
       for (int c = 0; c < nrhs; ++c) iters[c] += active[c];
       ++done_iters;
-      STCHK(read_state(true));
+      STCHK(read_state());
       bool more = false;
       for (int c = 0; c < nrhs; ++c) more = more || active[c];
       if (!more) {
