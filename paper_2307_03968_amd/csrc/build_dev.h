@@ -127,4 +127,16 @@ hipError_t launch_recompress(const AcaItem* items, int n_items, double eps, doub
 hipError_t launch_seg_copy(const double2* src, double2* dst, const int64_t* seg, int n_seg,
                            hipStream_t st);
 
+// One block of far-factor values: dst[dst + i + j dst_ld] (i < rows, j < cols)
+// from src (column-major, src_ld), or from its transpose; chi_off >= 0:
+// times chi[chi_off + j].
+struct PackItem {
+  const double2* src;
+  int64_t dst;
+  int32_t src_ld, dst_ld, rows, cols;
+  int32_t chi_off, trans;
+};
+hipError_t launch_pack(const PackItem* items, int n_items, const double* chi, double2* dst,
+                       hipStream_t st);
+
 }  // namespace hm

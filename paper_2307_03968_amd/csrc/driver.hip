@@ -247,6 +247,7 @@ struct hm_matrix {
     hm::GroupList sa;
   };
   std::vector<LevelList> nest_half;
+  std::shared_ptr<void> far_store;  // FarStore between the compression and the device part
   std::vector<std::vector<int32_t>> sa_rows_h;  // per one-RHS group and level: rows (as its tiles)
   // per-kernel timing
   bool prof = false;
@@ -1963,35 +1964,39 @@ int run_gemms(const double2* A, const double2* B, double2* C, const std::vector<
   return HM_OK;
 }
 
+// Far factors the compression left on the device: per compressed block its U
+// (m x r) followed by V (n x r), until the panels, stacks and groups are packed.
+struct FarStore {
+  std::vector<std::unique_ptr<DevTmp<double2>>> bufs;
+  std::vector<const double2*> u;
+};
+
+// The far factors of items to their places in dst (zeroed before).
+int pack_far(const std::vector<PackItem>& items, const double* d_chi, double2* dst, hipStream_t st) {
+  if (items.empty()) return HM_OK;
+  DevTmp<PackItem> di;
+  STCHK(di.alloc(items.size()));
+  HIPCHK(hipMemcpyAsync(di.p, items.data(), sizeof(PackItem) * items.size(), hipMemcpyHostToDevice, st));
+  for (size_t i0 = 0; i0 < items.size(); i0 += (size_t)1 << 30)
+    HIPCHK(launch_pack(di.p + i0, (int)std::min<size_t>(items.size() - i0, (size_t)1 << 30), d_chi,
+                       dst, st));
+  HIPCHK(hipStreamSynchronize(st));  // the item buffer is freed on return
+  return HM_OK;
+}
+
 // The apply panels and the LU blocks with the near entries computed on the
 // device: R64 (rtot elements and the zeroed pad) gets the near blocks of
-// every leaf (fills, as the panel assembly listed them) and the packed
-// far-factor columns (upack, leaf a at u_off[a], placed after the leaf's
-// diagonal and near columns); LU (lutot) gets each leaf's diagonal block
-// with leading dimension m_a.  Two distinct points closer than 1e-12 in a
-// near block are refused as on the host.
-int fill_near_device(hm_matrix* h, const std::vector<std::vector<FillItem>>& fills,
-                     const bigvec<double2>& upack, const std::vector<int64_t>& u_off,
-                     const std::vector<int64_t>& near_cols, const std::vector<int64_t>& R_off,
-                     int64_t rtot, const std::vector<int64_t>& LU_off, int64_t lutot,
-                     hipStream_t st) {
+// every leaf (fills, as the panel assembly listed them); LU (lutot) gets each
+// leaf's diagonal block with leading dimension m_a.  Two distinct points
+// closer than 1e-12 in a near block are refused as on the host.
+int fill_near_device(hm_matrix* h, const std::vector<std::vector<FillItem>>& fills, int64_t rtot,
+                     const std::vector<int64_t>& LU_off, int64_t lutot, hipStream_t st) {
   const HostH& H = h->H;
   const int nl = (int)H.leaf_size.size();
   const size_t rbytes = sizeof(double2) * std::max<int64_t>(rtot, 1) + kPanelPad;
   STCHK(dalloc(h, (void**)&h->R64, rbytes));
   HIPCHK(hipMemsetAsync(h->R64, 0, rbytes, st));
   STCHK(dalloc(h, (void**)&h->LU, sizeof(double2) * std::max<int64_t>(lutot, 1)));
-  // far-factor columns: one upload, then one segment per leaf
-  std::vector<int64_t> seg;
-  for (int a = 0; a < nl; ++a) {
-    const int64_t end = a + 1 < nl ? u_off[a + 1] : (int64_t)upack.size();
-    const int64_t ld = even_ld(H.leaf_size[a]);
-    if (end > u_off[a]) {
-      seg.push_back(u_off[a]);
-      seg.push_back(R_off[a] + (H.leaf_size[a] + near_cols[a]) * ld);
-      seg.push_back(end - u_off[a]);
-    }
-  }
   std::vector<FillItem> items, lu_items;
   for (int a = 0; a < nl; ++a) {
     items.insert(items.end(), fills[a].begin(), fills[a].end());
@@ -2000,14 +2005,10 @@ int fill_near_device(hm_matrix* h, const std::vector<std::vector<FillItem>>& fil
   std::vector<EntryInst> inst;
   for (const EntryParams& e : H.inst) inst.push_back({e.kind, 0, e.k, e.h});
   std::vector<int32_t> loff(H.leaf_off), lm(H.leaf_size);
-  DevTmp<double2> du;
-  DevTmp<int64_t> dseg;
   DevTmp<FillItem> ditems, dlu;
   DevTmp<double> dxyz, dchi;
   DevTmp<int32_t> dloff, dlm, dli, dbad;
   DevTmp<EntryInst> dinst;
-  STCHK(du.alloc(upack.size()));
-  STCHK(dseg.alloc(seg.size()));
   STCHK(ditems.alloc(items.size()));
   STCHK(dlu.alloc(lu_items.size()));
   STCHK(dxyz.alloc(H.xyz_tree.size()));
@@ -2020,8 +2021,6 @@ int fill_near_device(hm_matrix* h, const std::vector<std::vector<FillItem>>& fil
   auto put = [&](void* d, const void* s_, size_t bytes) {
     return bytes ? hipMemcpyAsync(d, s_, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
   };
-  HIPCHK(put(du.p, upack.data(), sizeof(double2) * upack.size()));
-  HIPCHK(put(dseg.p, seg.data(), sizeof(int64_t) * seg.size()));
   HIPCHK(put(ditems.p, items.data(), sizeof(FillItem) * items.size()));
   HIPCHK(put(dlu.p, lu_items.data(), sizeof(FillItem) * lu_items.size()));
   HIPCHK(put(dxyz.p, H.xyz_tree.data(), sizeof(double) * H.xyz_tree.size()));
@@ -2031,7 +2030,6 @@ int fill_near_device(hm_matrix* h, const std::vector<std::vector<FillItem>>& fil
   HIPCHK(put(dli.p, H.leaf_inst.data(), sizeof(int32_t) * H.leaf_inst.size()));
   HIPCHK(put(dinst.p, inst.data(), sizeof(EntryInst) * inst.size()));
   HIPCHK(hipMemsetAsync(dbad.p, 0, sizeof(int32_t), st));
-  HIPCHK(launch_seg_copy(du.p, h->R64, dseg.p, (int)(seg.size() / 3), st));
   const double* chi = H.chi_tree.empty() ? nullptr : dchi.p;
   for (size_t i0 = 0; i0 < items.size(); i0 += (size_t)1 << 30)
     HIPCHK(launch_fill_near(ditems.p + i0, (int)std::min<size_t>(items.size() - i0, (size_t)1 << 30),
@@ -2052,11 +2050,13 @@ int fill_near_device(hm_matrix* h, const std::vector<std::vector<FillItem>>& fil
 // (H.aca): cross approximation and recompression on the GPU in chunks of at
 // most kAcaChunkBytes of scratch, first with 32 columns per block, then with
 // kAcaMaxCols for the blocks that needed more; a block still short of
-// columns is compressed on the host by the same rules.
+// columns is compressed on the host by the same rules.  The factors stay on
+// the device (fs); the host keeps their ranks.
 constexpr int64_t kAcaChunkBytes = (int64_t)1 << 30;
 
-int device_aca(HostH& H, const hm_build_opts& o, hipStream_t st) {
+int device_aca(HostH& H, const hm_build_opts& o, FarStore& fs, hipStream_t st) {
   if (!H.aca_pending) return HM_OK;
+  fs.u.assign(H.lowrank.size(), nullptr);
   const int nb = (int)H.aca.size();
   std::vector<EntryInst> inst;
   for (const EntryParams& e : H.inst) inst.push_back({e.kind, 0, e.k, e.h});
@@ -2084,11 +2084,11 @@ int device_aca(HostH& H, const hm_build_opts& o, hipStream_t st) {
     }
     const int64_t cap = std::min<int64_t>(total, kAcaChunkBytes / (int64_t)sizeof(double2));
     // buffers of the pass, reused by its chunks (grown when a chunk needs more)
-    DevTmp<double2> ws, packed;
+    DevTmp<double2> ws;
     DevTmp<AcaItem> ditems;
     DevTmp<AcaOut> dout;
     DevTmp<int64_t> dseg;
-    int64_t ws_cap = 0, packed_cap = 0, items_cap = 0, out_cap = 0, seg_cap = 0;
+    int64_t ws_cap = 0, items_cap = 0, out_cap = 0, seg_cap = 0;
     auto grow = [&](auto& buf, int64_t& have, int64_t want) -> int {
       if (want <= have) return HM_OK;
       if (buf.p) HIPCHK(hipFree(buf.p));
@@ -2098,8 +2098,6 @@ int device_aca(HostH& H, const hm_build_opts& o, hipStream_t st) {
       have = want;
       return HM_OK;
     };
-    std::unique_ptr<char[]> host;
-    int64_t host_cap = 0;
     std::vector<int> retry;
     size_t b0 = 0;
     while (b0 < todo.size()) {
@@ -2128,7 +2126,7 @@ int device_aca(HostH& H, const hm_build_opts& o, hipStream_t st) {
       std::vector<AcaOut> res(ni);
       HIPCHK(hipMemcpyAsync(res.data(), dout.p, sizeof(AcaOut) * ni, hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
-      // the kept factors, packed U' then V' per block, in one download
+      // the kept factors, packed U' then V' per block
       std::vector<int64_t> seg, pos(ni, -1);
       int64_t ptot = 0;
       for (int q = 0; q < ni; ++q) {
@@ -2148,23 +2146,21 @@ int device_aca(HostH& H, const hm_build_opts& o, hipStream_t st) {
         seg.insert(seg.end(), {a.o_off + (int64_t)a.m * a.rcap, ptot + (int64_t)a.m * r, (int64_t)a.n * r});
         ptot += (int64_t)(a.m + a.n) * r;
       }
+      const double2* pk = nullptr;
       if (ptot > 0) {
-        STCHK(grow(packed, packed_cap, ptot));
+        fs.bufs.emplace_back(new DevTmp<double2>());
+        STCHK(fs.bufs.back()->alloc((size_t)ptot));
+        pk = fs.bufs.back()->p;
         STCHK(grow(dseg, seg_cap, (int64_t)seg.size()));
-        if (ptot > host_cap) {  // staging of the download, left uninitialised
-          host.reset(new char[(size_t)ptot * sizeof(double2)]);
-          host_cap = ptot;
-        }
         HIPCHK(hipMemcpyAsync(dseg.p, seg.data(), sizeof(int64_t) * seg.size(), hipMemcpyHostToDevice, st));
-        HIPCHK(launch_seg_copy(ws.p, packed.p, dseg.p, (int)(seg.size() / 3), st));
-        HIPCHK(hipMemcpyAsync(host.get(), packed.p, sizeof(double2) * ptot, hipMemcpyDeviceToHost, st));
+        HIPCHK(launch_seg_copy(ws.p, fs.bufs.back()->p, dseg.p, (int)(seg.size() / 3), st));
         HIPCHK(hipStreamSynchronize(st));
       }
-      const cplx* hp = reinterpret_cast<const cplx*>(host.get());
       for (int q = 0; q < ni; ++q) {
         if (res[q].status != 0) continue;
         const AcaItem& a = items[q];
-        LowRank& lr = H.lowrank[todo[b0 + q]];
+        const int b = todo[b0 + q];
+        LowRank& lr = H.lowrank[b];
         lr.m = a.m;
         lr.n = a.n;
         if (res[q].k < 1) {  // no pivot anywhere: a zero block of rank 1
@@ -2174,9 +2170,7 @@ int device_aca(HostH& H, const hm_build_opts& o, hipStream_t st) {
           continue;
         }
         lr.r = res[q].rank;
-        const cplx* src = hp + pos[q];
-        lr.U.assign(src, src + (size_t)a.m * lr.r);
-        lr.V.assign(src + (size_t)a.m * lr.r, src + (size_t)(a.m + a.n) * lr.r);
+        fs.u[b] = pk + pos[q];
       }
       b0 = b1;
     }
@@ -2195,6 +2189,24 @@ int device_aca(HostH& H, const hm_build_opts& o, hipStream_t st) {
     std::iota(rows.begin(), rows.end(), (int64_t)d.t_off);
     std::iota(cols.begin(), cols.end(), (int64_t)d.s_off);
     H.lowrank[q] = compress_block(pt, rows.data(), d.m, cols.data(), d.n, o.aca_tol, o.max_rank);
+  }
+  // zero blocks and those compressed on the host join the others
+  std::vector<double2> rest;
+  std::vector<std::pair<int, size_t>> rest_at;
+  for (int q = 0; q < nb; ++q) {
+    LowRank& lr = H.lowrank[q];
+    if (fs.u[q] || lr.r < 1) continue;
+    rest_at.push_back({q, rest.size()});
+    for (const std::vector<cplx>* f : {&lr.U, &lr.V})
+      for (const cplx& v : *f) rest.push_back(make_double2(v.real(), v.imag()));
+  }
+  if (!rest.empty()) {
+    fs.bufs.emplace_back(new DevTmp<double2>());
+    STCHK(fs.bufs.back()->alloc(rest.size()));
+    HIPCHK(hipMemcpyAsync(fs.bufs.back()->p, rest.data(), sizeof(double2) * rest.size(),
+                          hipMemcpyHostToDevice, st));
+    HIPCHK(hipStreamSynchronize(st));
+    for (const auto& ra : rest_at) fs.u[ra.first] = fs.bufs.back()->p + ra.second;
   }
   H.aca_pending = false;
   std::vector<HostH::AcaBlock>().swap(H.aca);
@@ -2622,6 +2634,29 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   auto lev_of = [&](int li) { return (h->lmin < 0) ? h->L + 1 : h->lmin + li; };
   auto rank = [&](int b) { return H.lowrank[H.far[b].src].r; };
   const double* chi = H.chi_tree.empty() ? nullptr : H.chi_tree.data();
+  // Blocks computed on the device (the handle keeps no host blocks): the host
+  // lists the near blocks for the device fill and the far factors for the
+  // device packing; otherwise it packs them itself.
+  const bool dev = H.near_on_device;
+  const FarStore* fs = static_cast<const FarStore*>(h->far_store.get());
+  if (dev && (!fs || fs->u.size() != H.lowrank.size())) {
+    set_error("internal: no device factors");
+    return HM_ESTATE;
+  }
+  // U (fb.m x r) and V (fb.n x r) of far block b's orientation on the device
+  auto dev_u = [&](int b) -> const double2* {
+    const FarBlock& fb = H.far[b];
+    return fs->u[fb.src] + (fb.transposed ? (int64_t)fb.n * rank(b) : 0);
+  };
+  auto dev_v = [&](int b) -> const double2* {
+    const FarBlock& fb = H.far[b];
+    return fs->u[fb.src] + (fb.transposed ? 0 : (int64_t)fb.m * rank(b));
+  };
+  // W_b (rank x n, times chi) at row `row` of a matrix of leading dimension ld
+  auto w_item = [&](int b, int64_t at, int32_t ld) -> PackItem {
+    const FarBlock& fb = H.far[b];
+    return {dev_v(b), at, fb.n, ld, rank(b), fb.n, chi ? fb.s_off : -1, 1};
+  };
   // W_b[q, j] = V[j, q] chi_s[j] of the stored orientation (n x r)
   auto wval = [&](int b, int q, int j) -> double2 {
     const FarBlock& fb = H.far[b];
@@ -2687,6 +2722,17 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       }
     }
   };
+  auto pack_W = [&](const GroupSet& gs) {
+    std::vector<PackItem> items;
+    for (int g = 0; g < (int)gs.groups.size(); ++g) {
+      int32_t row = 0;
+      for (int b : gs.blocks[g]) {
+        items.push_back(w_item(b, gs.groups[g].w_off + row, gs.groups[g].ld));
+        row += rank(b);
+      }
+    }
+    return items;
+  };
   auto fill_W = [&](const GroupSet& gs, bigvec<double2>& W) {
     W = bigvec<double2>((size_t)std::max<int64_t>(gs.wtot, 1));  // zeroed (pad rows stay 0)
     const int ng = (int)gs.groups.size();
@@ -2708,7 +2754,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   // one t region after the N tree-order rows serves both layouts
   h->T = std::max(gs1.T, gsm.T);
   bigvec<double2> W;
-  fill_W(gs1, W);
+  if (!dev) fill_W(gs1, W);
 
   // ---- per leaf: in-row blocks (finest first) and global slices (finest first)
   std::vector<std::vector<int>> inrow(nl);
@@ -2771,7 +2817,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
     irtot += (int64_t)ir_ld[a] * nmax;
     irrows += ir_cols[a];
   }
-  bigvec<double2> IR((size_t)std::max<int64_t>(irtot, 1));  // zeroed
+  bigvec<double2> IR((size_t)(dev ? 0 : std::max<int64_t>(irtot, 1)));  // zeroed
   std::vector<int32_t> ir_soff((size_t)std::max<int64_t>(irrows, 1)), ir_n((size_t)std::max<int64_t>(irrows, 1));
 #pragma omp parallel for schedule(dynamic, 1)
   for (int a = 0; a < nl; ++a) {
@@ -2781,7 +2827,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       for (int q = 0; q < rank(b); ++q, ++row) {
         ir_soff[ir_row0[a] + row] = fb.s_off;
         ir_n[ir_row0[a] + row] = fb.n;
-        for (int j = 0; j < fb.n; ++j) IR[ir_off[a] + row + (int64_t)j * ir_ld[a]] = wval(b, q, j);
+        for (int j = 0; j < fb.n && !dev; ++j) IR[ir_off[a] + row + (int64_t)j * ir_ld[a]] = wval(b, q, j);
       }
     }
   }
@@ -2806,37 +2852,25 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
     piv_off[a] = ptot;
     ptot += m;
   }
-  // Near entries computed on the device (the handle keeps no host blocks):
-  // the host packs only the far-factor columns of each panel, contiguous per
-  // leaf (u_off), and lists the near blocks for the device fill.
-  const bool dev_near = H.near_on_device;
-  std::vector<int64_t> u_off(nl, 0);
-  int64_t utot = 0;
-  for (int a = 0; a < nl; ++a) {
-    u_off[a] = utot;
-    utot += (int64_t)even_ld(H.leaf_size[a]) * (ir_cols[a] + gl_cols[a]);
-  }
-  bigvec<double2> R((size_t)std::max<int64_t>(dev_near ? utot : rtot, 1));  // zeroed (pad rows stay 0)
+  bigvec<double2> R((size_t)(dev ? 0 : std::max<int64_t>(rtot, 1)));  // zeroed (pad rows stay 0)
   std::vector<int32_t> src((size_t)std::max<int64_t>(ctot, 1)), src_mm(src.size());
-  bigvec<double2> D((size_t)(dev_near ? 0 : lutot));
+  bigvec<double2> D((size_t)(dev ? 0 : lutot));
   std::vector<std::vector<FillItem>> fills(nl);
+  std::vector<std::vector<PackItem>> upack(nl);
 #pragma omp parallel for schedule(dynamic, 1)
   for (int a = 0; a < nl; ++a) {
     const int m = H.leaf_size[a];
-    const int64_t ld = even_ld(m), c_u = m + near_cols[a];
-    // column c of the panel (near columns are not packed on the device path)
-    auto col = [&](int64_t c) {
-      return dev_near ? R.data() + u_off[a] + (c - c_u) * ld : R.data() + R_off[a] + c * ld;
-    };
+    const int64_t ld = even_ld(m);
+    auto col = [&](int64_t c) { return R.data() + R_off[a] + c * ld; };  // column c of the panel
     int32_t* S = src.data() + R_col[a];
     int32_t* S2 = src_mm.data() + R_col[a];
     int64_t c = 0;
     auto put_block = [&](const NearBlock& nb) {
       const int n = H.leaf_size[nb.s_leaf];
-      if (dev_near) fills[a].push_back({R_off[a] + c * ld, (int32_t)ld, a, nb.s_leaf, 0});
+      if (dev) fills[a].push_back({R_off[a] + c * ld, (int32_t)ld, a, nb.s_leaf, 0});
       for (int j = 0; j < n; ++j, ++c) {
         S[c] = S2[c] = H.leaf_off[nb.s_leaf] + j;
-        if (dev_near) continue;
+        if (dev) continue;
         const cplx* z = H.near_data.data() + nb.data + (size_t)j * m;
         double2* P = col(c);
         for (int i = 0; i < m; ++i) P[i] = make_double2(z[i].real(), z[i].imag());
@@ -2847,9 +2881,12 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       const FarBlock& fb = H.far[b];
       const LowRank& lr = H.lowrank[fb.src];
       const std::vector<cplx>& U = fb.transposed ? lr.V : lr.U;  // m_b x r
+      if (dev && lr.r > 0)
+        upack[a].push_back({dev_u(b) + row_in_block, R_off[a] + c * ld, fb.m, (int32_t)ld, m, lr.r, -1, 0});
       for (int q = 0; q < lr.r; ++q, ++c) {
         S[c] = src_base < 0 ? 0 : (int32_t)(src_base + q);
         S2[c] = src_mm_base + q;
+        if (dev) continue;
         double2* P = col(c);
         for (int i = 0; i < m; ++i) {
           const cplx v = U[row_in_block + i + (size_t)q * fb.m];
@@ -2858,7 +2895,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       }
     };
     put_block(H.near[diag_of[a]]);
-    if (!dev_near) {
+    if (!dev) {
       const cplx* z = H.near_data.data() + H.near[diag_of[a]].data;
       for (int64_t e = 0; e < (int64_t)m * m; ++e) D[LU_off[a] + e] = make_double2(z[e].real(), z[e].imag());
     }
@@ -2901,8 +2938,23 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   STCHK(upload(h, &h->perm, H.tree.perm, st));
   STCHK(upload(h, &h->leaf_off, loff, st));
   STCHK(upload(h, &h->leaf_m, lm, st));
-  if (dev_near) {
-    STCHK(fill_near_device(h, fills, R, u_off, near_cols, R_off, rtot, LU_off, lutot, st));
+  // far factors packed on the device into a zeroed array of n elements and a pad
+  DevTmp<double> d_chi;
+  if (dev && chi) {
+    STCHK(d_chi.alloc(H.chi_tree.size()));
+    HIPCHK(hipMemcpyAsync(d_chi.p, chi, sizeof(double) * H.chi_tree.size(), hipMemcpyHostToDevice, st));
+  }
+  auto packed = [&](double2** p, int64_t n, size_t pad, const std::vector<PackItem>& items) -> int {
+    const size_t bytes = sizeof(double2) * (size_t)std::max<int64_t>(n, 1) + pad;
+    STCHK(dalloc(h, (void**)p, bytes));
+    HIPCHK(hipMemsetAsync(*p, 0, bytes, st));
+    return pack_far(items, d_chi.p, *p, st);
+  };
+  if (dev) {
+    STCHK(fill_near_device(h, fills, rtot, LU_off, lutot, st));
+    std::vector<PackItem> items;
+    for (const auto& u : upack) items.insert(items.end(), u.begin(), u.end());
+    STCHK(pack_far(items, nullptr, h->R64, st));
   } else {
     STCHK(upload(h, &h->R64, R, st, false, kPanelPad));
   }
@@ -2915,17 +2967,31 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   STCHK(upload(h, &h->LU_off, LU_off, st));
   STCHK(upload(h, &h->Dinv_off, Dinv_off, st));
   STCHK(upload(h, &h->piv_off, piv_off, st));
-  if (!dev_near) STCHK(upload(h, &h->LU, D, st));
+  if (!dev) STCHK(upload(h, &h->LU, D, st));
   bigvec<double2>().swap(D);
-  STCHK(upload(h, &h->W64, W, st));
+  if (dev) STCHK(packed(&h->W64, gs1.wtot, 0, pack_W(gs1)));
+  else STCHK(upload(h, &h->W64, W, st));
   bigvec<double2>().swap(W);
   STCHK(upload(h, &h->groups, gs1.groups, st));
   STCHK(upload(h, &h->groups_mm, gsm.groups, st));
   STCHK(upload(h, &h->src_mm, src_mm, st));
-  fill_W(gsm, W);
-  STCHK(upload(h, &h->Wmm64, W, st, false, kPanelPad));
-  bigvec<double2>().swap(W);
-  STCHK(upload(h, &h->IR64, IR, st));
+  if (dev) {
+    STCHK(packed(&h->Wmm64, gsm.wtot, kPanelPad, pack_W(gsm)));
+    std::vector<PackItem> items;
+    for (int a = 0; a < nl; ++a) {
+      int32_t row = 0;
+      for (int b : inrow[a]) {
+        items.push_back(w_item(b, ir_off[a] + row, ir_ld[a]));
+        row += rank(b);
+      }
+    }
+    STCHK(packed(&h->IR64, irtot, 0, items));
+  } else {
+    fill_W(gsm, W);
+    STCHK(upload(h, &h->Wmm64, W, st, false, kPanelPad));
+    bigvec<double2>().swap(W);
+    STCHK(upload(h, &h->IR64, IR, st));
+  }
   bigvec<double2>().swap(IR);
   STCHK(upload(h, &h->ir_off, ir_off, st));
   STCHK(upload(h, &h->ir_ld, ir_ld, st));
@@ -3298,10 +3364,13 @@ static int device_part(hm_matrix* h, const hm_build_opts* opts, void* hip_stream
   HIPCHK(hipGetDevice(&h->device));
   if (h->H.aca_pending) {
     report(opts, "host build done, compressing far blocks on the device");
-    STCHK(device_aca(h->H, *opts, (hipStream_t)hip_stream));
+    auto fs = std::make_shared<FarStore>();
+    STCHK(device_aca(h->H, *opts, *fs, (hipStream_t)hip_stream));
+    h->far_store = fs;
   }
   report(opts, "packing and uploading blocks");
   STCHK(build_device(h, opts, (hipStream_t)hip_stream));
+  h->far_store.reset();
   report(opts, "device build done");
   if (!(opts->flags & HM_BUILD_KEEP_HOST)) {
     bigvec<cplx>().swap(h->H.near_data);
@@ -3925,7 +3994,9 @@ int build_host_phase(const hm_problem* prob, const hm_build_opts* opts, hm_matri
       }
       hipStream_t st = nullptr;
       HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
-      const int s = device_aca(h->H, *opts, st);
+      auto fs = std::make_shared<FarStore>();
+      const int s = device_aca(h->H, *opts, *fs, st);
+      h->far_store = fs;
       (void)hipStreamSynchronize(st);
       (void)hipStreamDestroy(st);
       STCHK(s);
