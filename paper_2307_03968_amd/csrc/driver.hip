@@ -64,6 +64,67 @@ struct GroupList {
 
 }  // namespace hm
 
+// Device memory of one owner, freed together.  A handle's arrays are cut from
+// few blocks (reserve, adopt): freeing a block of more than 64 MB takes 0.3 ms
+// whatever its size (a 5,800-point handle: 7.1 ms to release in a block per
+// array, 1.5 ms so).
+struct Slabs {
+  static constexpr size_t kBlock = (size_t)1 << 20;  // for arrays of at most a quarter of it
+  std::vector<void*> blocks;
+  char* cur = nullptr;
+  size_t left = 0;
+  Slabs() = default;
+  Slabs(const Slabs&) = delete;
+  Slabs& operator=(const Slabs&) = delete;
+  ~Slabs() { clear(); }
+  void clear() {
+    for (void* p : blocks) (void)hipFree(p);
+    blocks.clear();
+    cur = nullptr;
+    left = 0;
+  }
+  // A block for the next arrays, `bytes` in all; without memory for it they
+  // get blocks of their own.
+  void reserve(size_t bytes) {
+    void* b = nullptr;
+    if (bytes <= left) return;
+    if (hipMalloc(&b, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    blocks.push_back(b);
+    cur = static_cast<char*>(b);
+    left = bytes;
+  }
+  // A block that served something else, for the next arrays (not zeroed).
+  void adopt(void* b, size_t bytes) {
+    blocks.push_back(b);
+    cur = static_cast<char*>(b);
+    left = bytes / 256 * 256;
+  }
+  static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 16) + 255) / 256 * 256; }
+  hipError_t alloc(void** p, size_t bytes) {  // 256-byte aligned
+    bytes = rounded(bytes);
+    if (bytes > left && bytes <= kBlock / 4) reserve(kBlock);
+    if (bytes > left) {
+      const hipError_t e = hipMalloc(p, bytes);
+      if (e == hipSuccess) blocks.push_back(*p);
+      return e;
+    }
+    *p = cur;
+    cur += bytes;
+    left -= bytes;
+    return hipSuccess;
+  }
+};
+
+// Small host arrays on their way to the device: collected and copied in one
+// piece per owner (0: the handle, 1: the work lists).
+struct UploadBatch {
+  std::vector<char> host[2];
+  std::vector<std::pair<void**, size_t>> at[2];
+};
+
 struct hm_matrix {
   hm::HostH H;
   bool host_only = false;
@@ -77,7 +138,8 @@ struct hm_matrix {
   std::vector<int64_t> inst_off;
   double build_ms = 0;
   int64_t bytes = 0;
-  std::vector<void*> allocs;
+  Slabs mem;  // the handle's device arrays
+  UploadBatch* batch = nullptr;  // open while a build or a list rebuild runs
 
   // per leaf
   int64_t* perm = nullptr;
@@ -201,7 +263,7 @@ struct hm_matrix {
   std::vector<int64_t> R_off_h, R_col_h, M_off_h, M_col_h, Dinv_off_h;
   std::vector<int32_t> ir_ncol_h;
   std::vector<std::vector<int64_t>> ir_end, gl_end;
-  std::vector<void*> list_allocs;  // device work lists (rebuilt by hmat_tune)
+  Slabs list_mem;  // device work lists (rebuilt by hmat_tune)
   int64_t list_bytes = 0;
   int64_t partial_rows = 0;     // partial rows of the streaming lists, a column per right-hand side
   int64_t partial_rows_half = 0;  // of the half lists (one right-hand side)
@@ -228,9 +290,9 @@ struct hm_matrix {
   hm::NormItem* norm_items = nullptr;
   int32_t* norm_seg = nullptr;
   int n_norm_items = 0, nseg = 1;
-  std::vector<void*> ws_allocs;
+  Slabs ws_mem;
   // restarted GMRES: basis and preconditioned blocks, small per-column state
-  std::vector<void*> gm_allocs;
+  Slabs gm_mem;
   int gm_m = 0, gm_nrhs = 0;
   double2 *gm_V = nullptr, *gm_Z = nullptr, *gm_part = nullptr, *gm_h1 = nullptr,
           *gm_h2 = nullptr, *gm_hn = nullptr, *gm_bn = nullptr, *gm_y = nullptr;
@@ -258,12 +320,8 @@ struct hm_matrix {
   ~hm_matrix() {
     for (auto& r : prof_recs) { (void)hipEventDestroy(r.e0); (void)hipEventDestroy(r.e1); }
     for (auto e : ev_pool) (void)hipEventDestroy(e);
-    for (void* p : ws_allocs) (void)hipFree(p);
-    for (void* p : gm_allocs) (void)hipFree(p);
     if (gm_host) (void)hipHostFree(gm_host);
     if (nest_pool) (void)hipFree(nest_pool);
-    for (void* p : list_allocs) (void)hipFree(p);
-    for (void* p : allocs) (void)hipFree(p);
     if (norms_host) (void)hipHostFree(norms_host);
   }
 };
@@ -277,13 +335,12 @@ namespace {
 int dalloc(hm_matrix* h, void** p, size_t bytes, bool lists = false) {
   *p = nullptr;
   if (bytes == 0) bytes = 16;
-  hipError_t e = hipMalloc(p, bytes);
+  hipError_t e = (lists ? h->list_mem : h->mem).alloc(p, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     set_error("hipMalloc of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e));
     return HM_ENOMEM;
   }
-  (lists ? h->list_allocs : h->allocs).push_back(*p);
   h->bytes += (int64_t)bytes;
   if (lists) h->list_bytes += (int64_t)bytes;
   return HM_OK;
@@ -294,12 +351,53 @@ int dalloc(hm_matrix* h, void** p, size_t bytes, bool lists = false) {
 template <typename T, typename A>
 int upload(hm_matrix* h, T** dst, const std::vector<T, A>& v, hipStream_t st, bool lists = false,
            size_t pad = 0) {
-  STCHK(dalloc(h, (void**)dst, v.size() * sizeof(T) + pad, lists));
+  const size_t bytes = v.size() * sizeof(T);
+  if (h->batch && pad == 0 && bytes <= Slabs::kBlock / 4) {
+    std::vector<char>& b = h->batch->host[lists];
+    h->batch->at[lists].push_back({(void**)dst, b.size()});
+    *dst = nullptr;  // set by flush_uploads
+    b.resize((b.size() + std::max<size_t>(bytes, 16) + 255) / 256 * 256);
+    if (bytes) std::memcpy(b.data() + h->batch->at[lists].back().second, v.data(), bytes);
+    return HM_OK;
+  }
+  STCHK(dalloc(h, (void**)dst, bytes + pad, lists));
   if (!v.empty()) HIPCHK(hipMemcpyAsync(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, st));
   if (pad) HIPCHK(hipMemsetAsync(reinterpret_cast<char*>(*dst) + v.size() * sizeof(T), 0, pad, st));
   HIPCHK(hipStreamSynchronize(st));  // host vectors may be freed after return
   return HM_OK;
 }
+
+// The collected arrays to the device; their pointers are set.
+int flush_uploads(hm_matrix* h, hipStream_t st) {
+  if (!h->batch) return HM_OK;
+  for (int lists = 0; lists < 2; ++lists) {
+    std::vector<char>& b = h->batch->host[lists];
+    if (b.empty()) continue;
+    char* d = nullptr;
+    STCHK(dalloc(h, (void**)&d, b.size(), lists != 0));
+    HIPCHK(hipMemcpyAsync(d, b.data(), b.size(), hipMemcpyHostToDevice, st));
+    HIPCHK(hipStreamSynchronize(st));
+    for (const auto& a : h->batch->at[lists]) *a.first = d + a.second;
+    b.clear();
+    h->batch->at[lists].clear();
+  }
+  return HM_OK;
+}
+
+// Opens the handle's upload batch for the length of a scope (an outer one
+// stays in charge); what flush_uploads has not sent by then is dropped.
+struct BatchScope {
+  hm_matrix* h;
+  UploadBatch mine;
+  bool own;
+  explicit BatchScope(hm_matrix* h_) : h(h_), own(!h_->batch) {
+    if (own) h->batch = &mine;
+  }
+  BatchScope(const BatchScope&) = delete;
+  ~BatchScope() {
+    if (own) h->batch = nullptr;
+  }
+};
 
 int level_index(const hm_matrix* h, int level, int* li) {
   if (h->lmin < 0) {
@@ -705,19 +803,17 @@ hipError_t zero_words(void* p, int64_t n, hipStream_t st) {
 // counters and the zero rows are cleared on st, ahead of the solve's work.
 int ensure_workspace(hm_matrix* h, int nrhs, hipStream_t st) {
   if (nrhs <= h->ws_nrhs) return HM_OK;
-  for (void* p : h->ws_allocs) (void)hipFree(p);
-  h->ws_allocs.clear();
+  h->ws_mem.clear();
   h->ws_nrhs = 0;
   h->ws_bytes = 0;
   const int64_t ldin = h->N + h->T;
   auto al = [&](void** p, size_t bytes) -> int {
-    hipError_t e = hipMalloc(p, std::max<size_t>(bytes, 16));
+    hipError_t e = h->ws_mem.alloc(p, bytes);
     if (e != hipSuccess) {
       (void)hipGetLastError();
       set_error("workspace hipMalloc failed: " + std::string(hipGetErrorString(e)));
       return HM_ENOMEM;
     }
-    h->ws_allocs.push_back(*p);
     h->ws_bytes += (int64_t)std::max<size_t>(bytes, 16);
     return HM_OK;
   };
@@ -1286,20 +1382,18 @@ int ensure_gmres(hm_matrix* h, int m, int nrhs) {
   if (m <= h->gm_m && nrhs <= h->gm_nrhs) return HM_OK;
   m = std::max(m, h->gm_m);
   nrhs = std::max(nrhs, h->gm_nrhs);
-  for (void* p : h->gm_allocs) (void)hipFree(p);
-  h->gm_allocs.clear();
+  h->gm_mem.clear();
   if (h->gm_host) (void)hipHostFree(h->gm_host);
   h->gm_host = nullptr;
   h->gm_m = h->gm_nrhs = 0;
   const int64_t N = h->N, vs = N * nrhs;
   auto al = [&](void** p, size_t bytes) -> int {
-    hipError_t e = hipMalloc(p, std::max<size_t>(bytes, 16));
+    hipError_t e = h->gm_mem.alloc(p, bytes);
     if (e != hipSuccess) {
       (void)hipGetLastError();
       set_error("GMRES workspace hipMalloc failed: " + std::string(hipGetErrorString(e)));
       return HM_ENOMEM;
     }
-    h->gm_allocs.push_back(*p);
     return HM_OK;
   };
   const size_t c2 = sizeof(double2);
@@ -1556,6 +1650,7 @@ hipError_t dinv_pass(hm_matrix* h, const double2* in, const double2* v, double b
 int build_level_list(hm_matrix* h, int li, hipStream_t st) {
   hm_matrix::LevelList& LL = h->nest_half[li];
   if (LL.built) return HM_OK;
+  BatchScope batch(h);
   const int fine = li + 1;
   std::vector<std::vector<std::pair<int64_t, int64_t>>> dense(h->nl);
   std::vector<int64_t> irc(h->nl, 0);
@@ -1575,6 +1670,7 @@ int build_level_list(hm_matrix* h, int li, hipStream_t st) {
   }
   LL.sa.n = (int)items.size();
   STCHK(upload(h, &LL.sa.items, items, st, true));
+  STCHK(flush_uploads(h, st));
   LL.built = true;
   return HM_OK;
 }
@@ -1835,8 +1931,8 @@ int build_mm_multi(hm_matrix* h, int li, hipStream_t st) {
 // like the global ones), and the D^{-1} list.  Replaces earlier lists.
 int build_lists(hm_matrix* h, hipStream_t st) {
   HIPCHK(hipStreamSynchronize(st));
-  for (void* p : h->list_allocs) (void)hipFree(p);
-  h->list_allocs.clear();
+  BatchScope batch(h);
+  h->list_mem.clear();
   h->bytes -= h->list_bytes;
   h->list_bytes = 0;
   const int64_t old_rows = h->partial_rows, old_half = h->partial_rows_half, old_mm = h->partial_rows_mm;
@@ -1902,10 +1998,53 @@ int build_lists(hm_matrix* h, hipStream_t st) {
       for (int big = 0; big < 2; ++big)
         h->mm_series_wgs[f][big] = h->num_cus * series_mm_occupancy(f != 0, big ? 32 : 16);
   }
-  HIPCHK(hipStreamSynchronize(st));
+  STCHK(flush_uploads(h, st));
   if (h->partial_rows > old_rows || h->partial_rows_half > old_half || h->partial_rows_mm > old_mm)
     h->ws_nrhs = 0;  // the workspace is sized by the partial rows
   return HM_OK;
+}
+
+// Device bytes of a build's arrays (panels FP64 and FP32, D^{-1}-premultiplied
+// panels, LU and D^{-1}, stage-A W copies for both kernel families, in-row
+// stacks; then the half storage), from block sizes only, to within a few
+// percent; T: far coefficients.
+struct DataBytes {
+  int64_t panels, half, T;
+};
+DataBytes data_bytes(const hm_matrix* h) {
+  const HostH& H = h->H;
+  int64_t P = 0, Dm = 0, Wn = 0, T = 0, Hn = 0, Hc = 0;
+  const bool sym = h->want_half;  // half panels (surface, and volume on Z diag(1/chi))
+  for (const NearBlock& nb : H.near) {
+    const int64_t m = even_ld(H.leaf_size[nb.t_leaf]);
+    P += m * H.leaf_size[nb.s_leaf];
+    if (nb.t_leaf == nb.s_leaf) Dm += (int64_t)H.leaf_size[nb.t_leaf] * H.leaf_size[nb.t_leaf];
+    if (sym && nb.t_leaf < nb.s_leaf) {
+      Hn += m * H.leaf_size[nb.s_leaf];
+      Hc += H.leaf_size[nb.s_leaf];
+    }
+  }
+  int64_t Pf = 0;
+  for (const FarBlock& fb : H.far) {
+    const int64_t r = H.lowrank[fb.src].r;
+    P += r * fb.m;
+    Pf += r * fb.m;
+    Wn += r * fb.n;
+    T += r;
+  }
+  const int64_t f32 = h->has_f32 ? 1 : 0;
+  const int64_t bytes =
+      16 * (P + (P - Dm)) + 32 * Dm + 2 * 16 * Wn + f32 * (8 * (2 * P - Dm) + 2 * 8 * Wn);
+  // half panels, their sources and v slots, the scaled far data, the
+  // C^{-1}, C^{-T}, C and C^T panels and two N-vectors
+  const int64_t half =
+      Hn > 0 ? (16 + 8 * f32) * (Hn + Pf + Wn) + 20 * Hc + 32 * h->N + 64 * Dm : 0;
+  return {bytes, half, T};
+}
+
+// One block for arrays of about `bytes` (leading dimensions are rounded up).
+void reserve_data(hm_matrix* h, int64_t bytes) {
+  if (bytes > 0) h->mem.reserve((size_t)(bytes + bytes / 100) + Slabs::kBlock);
 }
 
 // Host layout of the far-field device arrays the half-storage data is
@@ -1921,18 +2060,34 @@ struct HalfSrc {
   const std::vector<std::vector<int>>* inrow;  // per leaf: in-row far blocks, in order
 };
 
+// While one is open on a thread, the thread's small DevTmp buffers share its
+// blocks, which are freed when it closes.
+struct TmpScope {
+  Slabs mem;
+  static thread_local TmpScope* open;
+  TmpScope* outer;
+  TmpScope() : outer(open) { open = this; }
+  TmpScope(const TmpScope&) = delete;
+  ~TmpScope() { open = outer; }
+};
+thread_local TmpScope* TmpScope::open = nullptr;
+
 // A temporary device buffer of the build (freed with the object).
 template <typename T>
 struct DevTmp {
   T* p = nullptr;
+  bool own = true;
   DevTmp() = default;
   DevTmp(const DevTmp&) = delete;
   DevTmp& operator=(const DevTmp&) = delete;
   ~DevTmp() {
-    if (p) (void)hipFree(p);
+    if (p && own) (void)hipFree(p);
   }
-  int alloc(size_t n) {
-    if (hipMalloc((void**)&p, sizeof(T) * std::max<size_t>(n, 1)) != hipSuccess) {
+  // keep: a block of its own (the pointer may be taken out of the object)
+  int alloc(size_t n, bool keep = false) {
+    const size_t bytes = sizeof(T) * std::max<size_t>(n, 1);
+    own = keep || !TmpScope::open || bytes > Slabs::kBlock / 4;
+    if ((own ? hipMalloc((void**)&p, bytes) : TmpScope::open->mem.alloc((void**)&p, bytes)) != hipSuccess) {
       (void)hipGetLastError();
       p = nullptr;
       set_error("hipMalloc of a build buffer failed");
@@ -1969,6 +2124,12 @@ int run_gemms(const double2* A, const double2* B, double2* C, const std::vector<
 struct FarStore {
   std::vector<std::unique_ptr<DevTmp<double2>>> bufs;
   std::vector<const double2*> u;
+  // the scratch of the compression, for the handle's arrays (keep_ws): the
+  // driver stalls for up to seconds where blocks are freed and allocated at
+  // more than some 80 GB/s, which builds in a row do without this
+  bool keep_ws = false;
+  DevTmp<double2> ws;
+  int64_t ws_bytes = 0;
 };
 
 // The far factors of items to their places in dst (zeroed before).
@@ -2174,6 +2335,11 @@ int device_aca(HostH& H, const hm_build_opts& o, FarStore& fs, hipStream_t st) {
       }
       b0 = b1;
     }
+    if (pass == 0 && fs.keep_ws) {
+      std::swap(fs.ws.p, ws.p);
+      std::swap(fs.ws.own, ws.own);
+      fs.ws_bytes = ws_cap * (int64_t)sizeof(double2);
+    }
     todo.swap(retry);
   }
   // blocks beyond the device's column limit
@@ -2283,11 +2449,11 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
   STCHK(d_choff.alloc(nl));
   STCHK(d_ok.alloc(nl));
   HIPCHK(hipMemcpyAsync(d_choff.p, ch_off.data(), sizeof(int64_t) * nl, hipMemcpyHostToDevice, st));
-  DevTmp<double2> cf, cft, ch, cht;
-  for (DevTmp<double2>* b : {&cf, &cft, &ch, &cht}) {
-    STCHK(b->alloc(chtot));
-    HIPCHK(hipMemsetAsync(b->p, 0, sizeof(double2) * std::max<int64_t>(chtot, 1), st));
-  }
+  DevTmp<double2> cpan;  // the four, handed to the handle below
+  const int64_t chld = (std::max<int64_t>(chtot, 1) + 15) / 16 * 16;  // 256-byte aligned
+  STCHK(cpan.alloc(4 * chld, true));
+  HIPCHK(hipMemsetAsync(cpan.p, 0, sizeof(double2) * 4 * chld, st));
+  double2 *const cf = cpan.p, *const cft = cf + chld, *const ch = cft + chld, *const cht = ch + chld;
   // volume: Z = A diag(chi) with A symmetric (the kernel part G and the
   // diagonal terms), so the scaled series runs on A: its blocks are the
   // panels' blocks with column j divided by chi_j (W' folds 1/chi into the
@@ -2299,8 +2465,8 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
     HIPCHK(hipMemcpyAsync(d_chi.p, H.chi_tree.data(), sizeof(double) * h->N,
                           hipMemcpyHostToDevice, st));
   }
-  HIPCHK(launch_csym(h->R64, h->R_off, h->leaf_m, h->leaf_off, d_chi.p, nl, h->max_m, cf.p, cft.p,
-                     ch.p, cht.p, d_choff.p, d_ok.p, st));
+  HIPCHK(launch_csym(h->R64, h->R_off, h->leaf_m, h->leaf_off, d_chi.p, nl, h->max_m, cf, cft,
+                     ch, cht, d_choff.p, d_ok.p, st));
   {
     std::vector<int32_t> ok(nl, 0);
     HIPCHK(hipMemcpyAsync(ok.data(), d_ok.p, sizeof(int32_t) * nl, hipMemcpyDeviceToHost, st));
@@ -2315,11 +2481,12 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
   DevTmp<double2> chx;
   if (vol) {
     STCHK(chx.alloc(chtot));
-    HIPCHK(launch_panel_scale(cht.p, cht.p, d_choff.p, h->leaf_m, h->leaf_off, d_chi.p, nl, 0, st));
-    HIPCHK(launch_panel_scale(ch.p, chx.p, d_choff.p, h->leaf_m, h->leaf_off, d_chi.p, nl, 1, st));
-    HIPCHK(launch_panel_scale(cft.p, cft.p, d_choff.p, h->leaf_m, h->leaf_off, d_chi.p, nl, 2, st));
+    HIPCHK(launch_panel_scale(cht, cht, d_choff.p, h->leaf_m, h->leaf_off, d_chi.p, nl, 0, st));
+    HIPCHK(launch_panel_scale(ch, chx.p, d_choff.p, h->leaf_m, h->leaf_off, d_chi.p, nl, 1, st));
+    HIPCHK(launch_panel_scale(cft, cft, d_choff.p, h->leaf_m, h->leaf_off, d_chi.p, nl, 2, st));
   }
-  const double2* ch_w = vol ? chx.p : ch.p;  // C^{-1} the pairs' W' meet
+  const double2* ch_w = vol ? chx.p : ch;  // C^{-1} the pairs' W' meet
+  reserve_data(h, data_bytes(h).half - 4 * (int64_t)sizeof(double2) * chld);
   // ---- half-panel layout
   std::vector<int64_t> hp_off(nl + 1, 0);
   std::vector<int32_t> hp_col(nl + 1, 0);
@@ -2379,8 +2546,8 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
         g2.push_back({c_off, ch_off[s], c_off, ldt, even_ld(ms), ldt, mt, ms, ms, 0, 0});
       }
     }
-    STCHK(run_gemms(ch.p, h->R64, tmp.p, g1, st));
-    STCHK(run_gemms(tmp.p, cht.p, h->H64, g2, st));
+    STCHK(run_gemms(ch, h->R64, tmp.p, g1, st));
+    STCHK(run_gemms(tmp.p, cht, h->H64, g2, st));
   }
   // ---- far part.  A far block whose row and column clusters are both
   // leaves (t, s) is a pair, stored once by its lower leaf t < s: U' =
@@ -2517,11 +2684,11 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
         wg.push_back({G.w_off + j0 * G.ld, ch_off[s], G.w_off + j0 * G.ld, G.ld, even_ld(ms), G.ld,
                       G.ld, ms, ms, 0, 0});
       });
-    STCHK(run_gemms(ch.p, h->R64, h->HF64, uf, st));
-    STCHK(run_gemms(ch.p, h->R64, h->FP64, up, st));
+    STCHK(run_gemms(ch, h->R64, h->HF64, uf, st));
+    STCHK(run_gemms(ch, h->R64, h->FP64, up, st));
     STCHK(run_gemms(ch_w, h->IR64, h->FP64, wp, st));
-    STCHK(run_gemms(h->IR64, cht.p, h->IRT64, wi, st));
-    STCHK(run_gemms(h->W64, cht.p, h->WT64, wg, st));
+    STCHK(run_gemms(h->IR64, cht, h->IRT64, wi, st));
+    STCHK(run_gemms(h->W64, cht, h->WT64, wg, st));
   }
   // per level: pairs and in-row rows of the far blocks of level >= l, and
   // the entries one half-storage term reads (near blocks s > t, pairs once,
@@ -2551,13 +2718,13 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
     h->ent_half[li] = e;
   }
   // ---- the factor panels move to the handle
-  for (auto pr : {std::make_pair(&ch, &h->CH), std::make_pair(&cht, &h->CHT),
-                  std::make_pair(&cf, &h->CF), std::make_pair(&cft, &h->CFT)}) {
-    *pr.second = pr.first->p;
-    pr.first->p = nullptr;
-    h->allocs.push_back(*pr.second);
-    h->bytes += (int64_t)sizeof(double2) * std::max<int64_t>(chtot, 1);
-  }
+  h->CH = ch;
+  h->CHT = cht;
+  h->CF = cf;
+  h->CFT = cft;
+  h->mem.blocks.push_back(cpan.p);
+  cpan.p = nullptr;
+  h->bytes += 4 * (int64_t)sizeof(double2) * chld;
   STCHK(dalloc(h, (void**)&h->hwork, sizeof(double2) * h->N));
   if (h->has_f32) {
     const int64_t n_ir = std::max<int64_t>(irtot, 1), n_w = std::max<int64_t>(wtot, 1);
@@ -2626,6 +2793,8 @@ void build_mark(const hm_build_opts* o, hipStream_t st, const char* what) {
 }
 
 int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
+  TmpScope tmp;
+  BatchScope batch(h);
   const HostH& H = h->H;
   const int nl = h->nl;
   const int64_t N = h->N;
@@ -2638,10 +2807,21 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   // lists the near blocks for the device fill and the far factors for the
   // device packing; otherwise it packs them itself.
   const bool dev = H.near_on_device;
-  const FarStore* fs = static_cast<const FarStore*>(h->far_store.get());
+  FarStore* fs = static_cast<FarStore*>(h->far_store.get());
   if (dev && (!fs || fs->u.size() != H.lowrank.size())) {
     set_error("internal: no device factors");
     return HM_ESTATE;
+  }
+  const int64_t need = data_bytes(h).panels;
+  if (dev && fs->ws.p && fs->ws_bytes <= need && fs->ws_bytes >= need / 2) {
+    h->mem.adopt(fs->ws.p, (size_t)fs->ws_bytes);
+    fs->ws.p = nullptr;
+  } else {
+    if (dev && fs->ws.p) {
+      (void)hipFree(fs->ws.p);
+      fs->ws.p = nullptr;
+    }
+    reserve_data(h, need);
   }
   // U (fb.m x r) and V (fb.n x r) of far block b's orientation on the device
   auto dev_u = [&](int b) -> const double2* {
@@ -2819,7 +2999,11 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   }
   bigvec<double2> IR((size_t)(dev ? 0 : std::max<int64_t>(irtot, 1)));  // zeroed
   std::vector<int32_t> ir_soff((size_t)std::max<int64_t>(irrows, 1)), ir_n((size_t)std::max<int64_t>(irrows, 1));
-#pragma omp parallel for schedule(dynamic, 1)
+  // Team threads spin for 0.2 s after a parallel region and then keep the HIP
+  // runtime's own threads from running (device phases of 1 ms took 0.15 to 2.5 s
+  // now and then), so without blocks to pack only very long lists get a team.
+  constexpr int64_t kParallelList = (int64_t)1 << 23;
+#pragma omp parallel for schedule(dynamic, 1) if (!dev || irrows > kParallelList)
   for (int a = 0; a < nl; ++a) {
     int32_t row = 0;
     for (int b : inrow[a]) {
@@ -2857,7 +3041,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   bigvec<double2> D((size_t)(dev ? 0 : lutot));
   std::vector<std::vector<FillItem>> fills(nl);
   std::vector<std::vector<PackItem>> upack(nl);
-#pragma omp parallel for schedule(dynamic, 1)
+#pragma omp parallel for schedule(dynamic, 1) if (!dev || ctot > kParallelList)
   for (int a = 0; a < nl; ++a) {
     const int m = H.leaf_size[a];
     const int64_t ld = even_ld(m);
@@ -3005,6 +3189,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   STCHK(dalloc(h, (void**)&h->M64, sizeof(double2) * std::max<int64_t>(mtot, 1) + kPanelPad));
   HIPCHK(hipMemsetAsync(h->M64, 0, sizeof(double2) * std::max<int64_t>(mtot, 1) + kPanelPad, st));
 
+  STCHK(flush_uploads(h, st));
   build_mark(opts, st, "panels packed and uploaded");
   // ---- leaf LU with partial pivoting, then D^{-1} (eq. 12's near inverse)
   int* info = nullptr;
@@ -3031,6 +3216,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   int32_t *d_tiles = nullptr, *d_ncm = nullptr;
   STCHK(upload(h, &d_tiles, tiles, st));
   STCHK(upload(h, &d_ncm, ncm, st));
+  STCHK(flush_uploads(h, st));
   HIPCHK(launch_premul(h->Dinv, h->Dinv_off, h->R64, h->R_off, h->leaf_m, d_ncm, h->M64, h->M_off,
                        d_tiles, (int)(tiles.size() / 2), h->max_m, st));
 
@@ -3139,8 +3325,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
     STCHK(build_half(h, hs, st));
     build_mark(opts, st, "half-storage data done");
   }
-  STCHK(build_lists(h, st));
-  HIPCHK(hipStreamSynchronize(st));
+  STCHK(build_lists(h, st));  // sends what is left of the batch too
   return HM_OK;
 }
 
@@ -3365,6 +3550,7 @@ static int device_part(hm_matrix* h, const hm_build_opts* opts, void* hip_stream
   if (h->H.aca_pending) {
     report(opts, "host build done, compressing far blocks on the device");
     auto fs = std::make_shared<FarStore>();
+    fs->keep_ws = true;
     STCHK(device_aca(h->H, *opts, *fs, (hipStream_t)hip_stream));
     h->far_store = fs;
   }
@@ -4020,39 +4206,11 @@ int build_device_phase(hm_matrix_t h, const hm_build_opts* opts, void* hip_strea
   });
 }
 
-// Device bytes the device part of the build will allocate (panels FP64 and
-// FP32, D^{-1}-premultiplied panels, LU and D^{-1}, stage-A W copies for both
-// kernel families, in-row stacks), plus the workspace for nrhs right-hand
-// sides; from block sizes only, to within a few percent.
+// Device bytes the device part of the build will allocate, plus the workspace
+// for nrhs right-hand sides.
 int64_t device_bytes_estimate(hm_matrix_t h, int nrhs) {
-  const HostH& H = h->H;
-  int64_t P = 0, Dm = 0, Wn = 0, T = 0, Hn = 0, Hc = 0;
-  const bool sym = h->want_half;  // half panels (surface, and volume on Z diag(1/chi))
-  for (const NearBlock& nb : H.near) {
-    const int64_t m = even_ld(H.leaf_size[nb.t_leaf]);
-    P += m * H.leaf_size[nb.s_leaf];
-    if (nb.t_leaf == nb.s_leaf) Dm += (int64_t)H.leaf_size[nb.t_leaf] * H.leaf_size[nb.t_leaf];
-    if (sym && nb.t_leaf < nb.s_leaf) {
-      Hn += m * H.leaf_size[nb.s_leaf];
-      Hc += H.leaf_size[nb.s_leaf];
-    }
-  }
-  int64_t Pf = 0;
-  for (const FarBlock& fb : H.far) {
-    const int64_t r = H.lowrank[fb.src].r;
-    P += r * fb.m;
-    Pf += r * fb.m;
-    Wn += r * fb.n;
-    T += r;
-  }
-  const int64_t f32 = h->has_f32 ? 1 : 0;
-  const int64_t bytes =
-      16 * (P + (P - Dm)) + 32 * Dm + 2 * 16 * Wn + f32 * (8 * (2 * P - Dm) + 2 * 8 * Wn);
-  // half panels, their sources and v slots, the scaled far data, the
-  // C^{-1}, C^{-T}, C and C^T panels and two N-vectors
-  const int64_t half =
-      Hn > 0 ? (16 + 8 * f32) * (Hn + Pf + Wn) + 20 * Hc + 32 * h->N + 64 * Dm : 0;
-  return bytes + half + workspace_bytes(h, nrhs, T);
+  const DataBytes d = data_bytes(h);
+  return d.panels + d.half + workspace_bytes(h, nrhs, d.T);
 }
 
 // Workspace of ensure_workspace for nrhs right-hand sides (t rows T when

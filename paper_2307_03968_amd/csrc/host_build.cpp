@@ -64,7 +64,7 @@ int build_host(const Problem& p, const hm_build_opts& o, HostH& H) {
   // build computes them (it also rejects coincident points there)
   const int64_t nfill = H.near_on_device ? 0 : (int64_t)H.near.size();
   if (nfill) H.near_data = bigvec<cplx>((size_t)tot);
-#pragma omp parallel for schedule(dynamic, 4) num_threads(nthreads)
+#pragma omp parallel for schedule(dynamic, 4) num_threads(nthreads) if (nfill > 0)
   for (int64_t q = 0; q < nfill; ++q) {
     const NearBlock& nb = H.near[q];
     const int m = H.leaf_size[nb.t_leaf], n = H.leaf_size[nb.s_leaf];
@@ -109,7 +109,7 @@ int build_host(const Problem& p, const hm_build_opts& o, HostH& H) {
       H.aca.push_back({ct.off, ct.size, cs.off, cs.size, 0});
     }
   const int64_t ncomp = H.aca_pending ? 0 : (int64_t)primary.size();
-#pragma omp parallel for schedule(dynamic, 1) num_threads(nthreads)
+#pragma omp parallel for schedule(dynamic, 1) num_threads(nthreads) if (ncomp > 0)
   for (int64_t q = 0; q < ncomp; ++q) {
     const auto& bp = far[primary[q]];
     const Cluster& ct = tr.nodes[bp.t];
