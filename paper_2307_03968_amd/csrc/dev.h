@@ -226,7 +226,7 @@ constexpr int kMaxVLeaves = 8;  // target leaves (blocks) per kind-2 or kind-3 p
 constexpr int kHalfMaxLeaf = 128;  // largest leaf the half-storage product serves
 constexpr int kHalfChunk = 1024;   // input columns of a kind-0 half-list piece (at most)
 constexpr int kHalfPieceCols = 256;  // half-panel columns of a kind-2 piece (at most)
-constexpr int kHalfPiecePairs = 4;   // far pairs of a kind-3 piece (at most): one per wave
+constexpr int kHalfPiecePairs = 8;   // far pairs of a kind-3 piece (at most)
 constexpr int kHalfInRowTile = 128;  // W-stack rows of a half-list in-row piece (at most)
 
 constexpr int kInRowTile = 64;   // stack rows per kind-1 piece (one row per lane)

@@ -69,7 +69,6 @@ struct GroupList {
 // whatever its size (a 5,800-point handle: 7.1 ms to release in a block per
 // array, 1.5 ms so).
 struct Slabs {
-  static constexpr size_t kBlock = (size_t)1 << 20;  // for arrays of at most a quarter of it
   std::vector<void*> blocks;
   char* cur = nullptr;
   size_t left = 0;
@@ -83,8 +82,8 @@ struct Slabs {
     cur = nullptr;
     left = 0;
   }
-  // A block for the next arrays, `bytes` in all; without memory for it they
-  // get blocks of their own.
+  // A block for the next arrays, `bytes` in all; without memory for it, and
+  // beyond it, they get blocks of their own.
   void reserve(size_t bytes) {
     void* b = nullptr;
     if (bytes <= left) return;
@@ -105,7 +104,6 @@ struct Slabs {
   static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 16) + 255) / 256 * 256; }
   hipError_t alloc(void** p, size_t bytes) {  // 256-byte aligned
     bytes = rounded(bytes);
-    if (bytes > left && bytes <= kBlock / 4) reserve(kBlock);
     if (bytes > left) {
       const hipError_t e = hipMalloc(p, bytes);
       if (e == hipSuccess) blocks.push_back(*p);
@@ -121,6 +119,7 @@ struct Slabs {
 // Small host arrays on their way to the device: collected and copied in one
 // piece per owner (0: the handle, 1: the work lists).
 struct UploadBatch {
+  static constexpr size_t kSmall = (size_t)256 << 10;
   std::vector<char> host[2];
   std::vector<std::pair<void**, size_t>> at[2];
 };
@@ -352,7 +351,7 @@ template <typename T, typename A>
 int upload(hm_matrix* h, T** dst, const std::vector<T, A>& v, hipStream_t st, bool lists = false,
            size_t pad = 0) {
   const size_t bytes = v.size() * sizeof(T);
-  if (h->batch && pad == 0 && bytes <= Slabs::kBlock / 4) {
+  if (h->batch && pad == 0 && bytes <= UploadBatch::kSmall) {
     std::vector<char>& b = h->batch->host[lists];
     h->batch->at[lists].push_back({(void**)dst, b.size()});
     *dst = nullptr;  // set by flush_uploads
@@ -506,19 +505,23 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     // piece from a queue): pieces of bounded size, largest estimated cost
     // first so that the last pieces taken are small.
     std::vector<std::pair<int64_t, TermItem>> pcs;
-    // piece sizes by the size of the list: about 1,400 half-panel pieces of 96
-    // to kHalfPieceCols columns, and two to kHalfPiecePairs pairs.  Wide pieces
-    // cost the least per byte, but a short list then leaves workgroups idle
-    // and every term waits for its last piece (four terms, FP64, 256 columns
-    // and 8 pairs against this rule: sphere 1,536 132 -> 82 us a solve, 6,000
-    // 195 -> 149, 12,000 296 -> 265, 24,576 417 -> 408; cube 17^3 275 -> 218,
-    // 24^3 603 -> 600).
+    // Piece sizes by the size of the list.  Wide pieces cost the least per byte,
+    // but a short list then leaves workgroups idle and every term waits for its
+    // last piece: about 700 half-panel pieces of 96 to kHalfPieceCols columns.
+    // Far pairs come in fours (one per wave) or, in short lists, twos; eights
+    // (kHalfPiecePairs) where the list is long, or of middle length beside wide
+    // half-panel pieces.  Four terms, FP64 / FP32, us, pieces of 256 columns and
+    // 8 pairs against this rule: sphere 1,536 133/135 -> 82/80, 6,000 195/167 ->
+    // 150/138, 9,358 251/211 -> 230/177, 16,000 368/273 both, 24,576 415/290 ->
+    // 406/286; cube 17^3 275/254 -> 229/183, 22^3 451/347 -> 439/313, 31^3
+    // 1,955/1,283 both (fours cost it 2,027/1,326; 1,400 pieces cost 16,000
+    // points 417/313).
     int64_t ncols = 0, npair = 0;
     for (const Seg& sg : segs) (sg.kind == 2 ? ncols : npair) += sg.kind >= 2 ? sg.u1 - sg.u0 : 0;
     const int64_t half_cols =
-        std::max<int64_t>(96, std::min<int64_t>(kHalfPieceCols, (ncols / 1400 + 31) / 32 * 32));
-    const int64_t half_pairs =
-        std::max<int64_t>(2, std::min<int64_t>(kHalfPiecePairs, (npair + 255) / 256));
+        std::max<int64_t>(96, std::min<int64_t>(kHalfPieceCols, (ncols / 700 + 31) / 32 * 32));
+    const bool eights = npair >= 3584 || (half_cols >= 224 && npair >= 1024 && npair < 2048);
+    const int64_t half_pairs = eights ? kHalfPiecePairs : (npair > 512 ? 4 : 2);
     for (const Seg& sg : segs) {
       const int m = h->H.leaf_size[sg.leaf];
       int64_t u = sg.u0;
@@ -2044,7 +2047,7 @@ DataBytes data_bytes(const hm_matrix* h) {
 
 // One block for arrays of about `bytes` (leading dimensions are rounded up).
 void reserve_data(hm_matrix* h, int64_t bytes) {
-  if (bytes > 0) h->mem.reserve((size_t)(bytes + bytes / 100) + Slabs::kBlock);
+  if (bytes > 0) h->mem.reserve((size_t)(bytes + bytes / 100) + ((size_t)1 << 20));
 }
 
 // Host layout of the far-field device arrays the half-storage data is
@@ -2060,34 +2063,18 @@ struct HalfSrc {
   const std::vector<std::vector<int>>* inrow;  // per leaf: in-row far blocks, in order
 };
 
-// While one is open on a thread, the thread's small DevTmp buffers share its
-// blocks, which are freed when it closes.
-struct TmpScope {
-  Slabs mem;
-  static thread_local TmpScope* open;
-  TmpScope* outer;
-  TmpScope() : outer(open) { open = this; }
-  TmpScope(const TmpScope&) = delete;
-  ~TmpScope() { open = outer; }
-};
-thread_local TmpScope* TmpScope::open = nullptr;
-
 // A temporary device buffer of the build (freed with the object).
 template <typename T>
 struct DevTmp {
   T* p = nullptr;
-  bool own = true;
   DevTmp() = default;
   DevTmp(const DevTmp&) = delete;
   DevTmp& operator=(const DevTmp&) = delete;
   ~DevTmp() {
-    if (p && own) (void)hipFree(p);
+    if (p) (void)hipFree(p);
   }
-  // keep: a block of its own (the pointer may be taken out of the object)
-  int alloc(size_t n, bool keep = false) {
-    const size_t bytes = sizeof(T) * std::max<size_t>(n, 1);
-    own = keep || !TmpScope::open || bytes > Slabs::kBlock / 4;
-    if ((own ? hipMalloc((void**)&p, bytes) : TmpScope::open->mem.alloc((void**)&p, bytes)) != hipSuccess) {
+  int alloc(size_t n) {
+    if (hipMalloc((void**)&p, sizeof(T) * std::max<size_t>(n, 1)) != hipSuccess) {
       (void)hipGetLastError();
       p = nullptr;
       set_error("hipMalloc of a build buffer failed");
@@ -2337,7 +2324,6 @@ int device_aca(HostH& H, const hm_build_opts& o, FarStore& fs, hipStream_t st) {
     }
     if (pass == 0 && fs.keep_ws) {
       std::swap(fs.ws.p, ws.p);
-      std::swap(fs.ws.own, ws.own);
       fs.ws_bytes = ws_cap * (int64_t)sizeof(double2);
     }
     todo.swap(retry);
@@ -2451,7 +2437,7 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
   HIPCHK(hipMemcpyAsync(d_choff.p, ch_off.data(), sizeof(int64_t) * nl, hipMemcpyHostToDevice, st));
   DevTmp<double2> cpan;  // the four, handed to the handle below
   const int64_t chld = (std::max<int64_t>(chtot, 1) + 15) / 16 * 16;  // 256-byte aligned
-  STCHK(cpan.alloc(4 * chld, true));
+  STCHK(cpan.alloc(4 * chld));
   HIPCHK(hipMemsetAsync(cpan.p, 0, sizeof(double2) * 4 * chld, st));
   double2 *const cf = cpan.p, *const cft = cf + chld, *const ch = cft + chld, *const cht = ch + chld;
   // volume: Z = A diag(chi) with A symmetric (the kernel part G and the
@@ -2793,7 +2779,6 @@ void build_mark(const hm_build_opts* o, hipStream_t st, const char* what) {
 }
 
 int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
-  TmpScope tmp;
   BatchScope batch(h);
   const HostH& H = h->H;
   const int nl = h->nl;
