@@ -821,6 +821,19 @@ int ensure_workspace(hm_matrix* h, int nrhs, hipStream_t st) {
     return HM_OK;
   };
   const int64_t ldr = row_ld(nrhs);
+  // one block from 16 MB on: a first solve then pays the driver once (24,576
+  // points, first series 1,000 -> 600 us, first product 850 -> 420; below, the
+  // runtime's own small blocks are quicker: 1,536 points 190 against 470 us)
+  {
+    size_t sum = 0;
+    for (size_t b : {sizeof(double2) * ldin * nrhs * 2, sizeof(double2) * (ldin + 1) * ldr * 2,
+                     sizeof(float2) * (ldin + 1) * ldr * 2, sizeof(double2) * h->N * nrhs * 4,
+                     sizeof(double2) * partial_entries(h, nrhs),
+                     sizeof(double) * (h->n_norm_items + h->nseg) * nrhs * 2,
+                     sizeof(int32_t) * counter_count(h, nrhs)})
+      sum += b;
+    if (sum >= (size_t)16 << 20) h->ws_mem.reserve(sum + 14 * 256);  // fourteen arrays
+  }
   STCHK(al((void**)&h->xin0, sizeof(double2) * ldin * nrhs));
   STCHK(al((void**)&h->xin1, sizeof(double2) * ldin * nrhs));
   // row-layout vectors: rows [y | t] plus one row of zeros (zrow = N + T)
