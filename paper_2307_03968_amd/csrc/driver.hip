@@ -2997,9 +2997,8 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   }
   bigvec<double2> IR((size_t)(dev ? 0 : std::max<int64_t>(irtot, 1)));  // zeroed
   std::vector<int32_t> ir_soff((size_t)std::max<int64_t>(irrows, 1)), ir_n((size_t)std::max<int64_t>(irrows, 1));
-  // Team threads spin for 0.2 s after a parallel region and then keep the HIP
-  // runtime's own threads from running (device phases of 1 ms took 0.15 to 2.5 s
-  // now and then), so without blocks to pack only very long lists get a team.
+  // A team's threads spin for 0.2 s after a parallel region (sixteen of them for
+  // a build of 10 ms), so without blocks to pack only very long lists get one.
   constexpr int64_t kParallelList = (int64_t)1 << 23;
 #pragma omp parallel for schedule(dynamic, 1) if (!dev || irrows > kParallelList)
   for (int a = 0; a < nl; ++a) {
