@@ -215,3 +215,6 @@ int export_host(const HostH& H, const char* path, const std::vector<cplx>* lu_ho
                 const std::vector<int32_t>* piv_host);
 
 }  // namespace hm
+
+// Not part of the public interface: for the tests.
+extern "C" int hm_debug_gave_up(hm_matrix_t h);
