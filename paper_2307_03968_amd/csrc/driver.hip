@@ -301,11 +301,14 @@ struct hm_matrix {
   double2* nest_pool = nullptr;
   int nest_cap = 0, nest_nrhs = 0;
   // half lists of the far blocks of exactly one level and their stage-A tiles
-  // (nested solves; made by the first one that needs the level)
+  // (nested solves; made by the first one that needs the level).  Their
+  // partial rows are their own: the workspace stays where it is, as graphs
+  // captured before refer to it
   struct LevelList {
     bool built = false;
     HalfList hl;
     hm::GroupList sa;
+    double2* partial = nullptr;  // the list's partial rows
   };
   std::vector<LevelList> nest_half;
   std::shared_ptr<void> far_store;  // FarStore between the compression and the device part
@@ -763,6 +766,7 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     STCHK(upload(h, &hl->lcnt, lcnt, st, true));
     STCHK(upload(h, &hl->vleaf, vleaf, st, true));
   }
+  if (ff) return HM_OK;  // partial rows of its own (build_level_list)
   int64_t& max_rows = mm ? h->partial_rows_mm : (hl ? h->partial_rows_half : h->partial_rows);
   max_rows = std::max(max_rows, rows);
   return HM_OK;
@@ -1686,6 +1690,7 @@ int build_level_list(hm_matrix* h, int li, hipStream_t st) {
   }
   LL.sa.n = (int)items.size();
   STCHK(upload(h, &LL.sa.items, items, st, true));
+  STCHK(dalloc(h, (void**)&LL.partial, sizeof(double2) * LL.hl.tl.rows, true));
   STCHK(flush_uploads(h, st));
   LL.built = true;
   return HM_OK;
@@ -1796,6 +1801,7 @@ struct NestedHalf {
         in = h->xin1;
       }
       HalfArgs ha = half_args(h, LL.hl, f32, in, ldin);
+      ha.t.partial = LL.partial;
       ha.t.alpha = -1.0;
       ha.t.yout = h->xin0;
       ha.t.ldy = ldin;
@@ -1856,7 +1862,6 @@ int nested_solve(hm_matrix* h, int level, bool f32, int K, const double2* b_dev,
   }
   if (use_half(h, 0, nrhs)) {
     bool lists = true;
-    const int64_t rows = h->partial_rows_half;
     for (int j = 1; j < n && lists; ++j) {
       const int li = ns.li(ns.lev[j]);
       if (h->nest_half[li].built) continue;
@@ -1865,10 +1870,6 @@ int nested_solve(hm_matrix* h, int level, bool f32, int K, const double2* b_dev,
       HIPCHK(hipStreamIsCapturing(st, &cs));
       lists = cs == hipStreamCaptureStatusNone;
       if (lists) STCHK(build_level_list(h, li, st));
-    }
-    if (h->partial_rows_half > rows) {  // the workspace is sized by the partial rows
-      h->ws_nrhs = 0;
-      STCHK(ensure_workspace(h, nrhs, st));
     }
     if (lists) {
       NestedHalf nh{h, f32, K, st, ns.lev};
