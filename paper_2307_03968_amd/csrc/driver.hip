@@ -264,6 +264,8 @@ struct hm_matrix {
   std::vector<std::vector<int64_t>> ir_end, gl_end;
   Slabs list_mem;  // device work lists (rebuilt by hmat_tune)
   int64_t list_bytes = 0;
+  bool lists_ok = false;   // false while, and after, a rebuild that failed
+  bool fail_lists = false; // tests: the next upload of work lists fails
   int64_t partial_rows = 0;     // partial rows of the streaming lists, a column per right-hand side
   int64_t partial_rows_half = 0;  // of the half lists (one right-hand side)
   int64_t partial_rows_mm = 0;  // of the matrix-core lists, in row layout
@@ -375,6 +377,11 @@ int flush_uploads(hm_matrix* h, hipStream_t st) {
   for (int lists = 0; lists < 2; ++lists) {
     std::vector<char>& b = h->batch->host[lists];
     if (b.empty()) continue;
+    if (lists && h->fail_lists) {
+      h->fail_lists = false;
+      set_error("upload of the work lists failed (asked for by a test)");
+      return HM_ENOMEM;
+    }
     char* d = nullptr;
     STCHK(dalloc(h, (void**)&d, b.size(), lists != 0));
     HIPCHK(hipMemcpyAsync(d, b.data(), b.size(), hipMemcpyHostToDevice, st));
@@ -400,6 +407,12 @@ struct BatchScope {
     if (own) h->batch = nullptr;
   }
 };
+
+int lists_usable(const hm_matrix* h) {
+  if (h->lists_ok) return HM_OK;
+  set_error("the work lists are missing after a failed rebuild; hmat_tune builds them again");
+  return HM_ESTATE;
+}
 
 int level_index(const hm_matrix* h, int level, int* li) {
   if (h->lmin < 0) {
@@ -1946,9 +1959,15 @@ int build_mm_multi(hm_matrix* h, int li, hipStream_t st) {
 // persistent workgroups): one-RHS lists (dense column ranges + in-row stack
 // rows), many-RHS lists (dense column ranges only: in-row U columns read t
 // like the global ones), and the D^{-1} list.  Replaces earlier lists.
+// A rebuild that fails leaves lists without data: lists_ok keeps calls off
+// them until a later rebuild succeeds, and the workspace, sized by the lists'
+// partial rows, is made anew.
 int build_lists(hm_matrix* h, hipStream_t st) {
   HIPCHK(hipStreamSynchronize(st));
   BatchScope batch(h);
+  h->lists_ok = false;
+  const int ws_nrhs = h->ws_nrhs;
+  h->ws_nrhs = 0;
   h->list_mem.clear();
   h->bytes -= h->list_bytes;
   h->list_bytes = 0;
@@ -2016,8 +2035,9 @@ int build_lists(hm_matrix* h, hipStream_t st) {
         h->mm_series_wgs[f][big] = h->num_cus * series_mm_occupancy(f != 0, big ? 32 : 16);
   }
   STCHK(flush_uploads(h, st));
-  if (h->partial_rows > old_rows || h->partial_rows_half > old_half || h->partial_rows_mm > old_mm)
-    h->ws_nrhs = 0;  // the workspace is sized by the partial rows
+  if (h->partial_rows <= old_rows && h->partial_rows_half <= old_half && h->partial_rows_mm <= old_mm)
+    h->ws_nrhs = ws_nrhs;  // the workspace still holds the partial rows
+  h->lists_ok = true;
   return HM_OK;
 }
 
@@ -3389,13 +3409,14 @@ using namespace hm;
 
 // ====================================================================== C-ABI
 namespace hm {
-// Host allocation failures inside a build surface as HM_ENOMEM.
+// Host allocation failures inside a build, or a call that makes work lists,
+// surface as HM_ENOMEM.
 template <typename F>
 int guarded(F&& f) {
   try {
     return f();
   } catch (const std::bad_alloc&) {
-    set_error("host memory exhausted during the build");
+    set_error("host memory exhausted");
     return HM_ENOMEM;
   }
 }
@@ -3653,6 +3674,7 @@ int hmat_apply(hm_matrix_t h, int32_t level, int32_t precision, const void* x_de
   const bool f32 = precision == HM_F32_APPLY;
   if (f32 && !h->has_f32) { set_error("FP32 copies were not kept"); return HM_ESTATE; }
   if (nrhs == 0) return HM_OK;
+  STCHK(lists_usable(h));
   int li = 0;
   STCHK(level_index(h, level, &li));
   HIPCHK(hipSetDevice(h->device));
@@ -3701,6 +3723,7 @@ static int ps_solve_impl(hm_matrix_t h, const ps_opts* o, const void* b_dev, int
   const bool f32 = o->precision == HM_F32_APPLY;
   if (f32 && !h->has_f32) { set_error("FP32 copies were not kept"); return HM_ESTATE; }
   if (nrhs == 0) return HM_OK;
+  STCHK(lists_usable(h));
   int li = 0;
   STCHK(level_index(h, o->level, &li));
   HIPCHK(hipSetDevice(h->device));
@@ -3903,7 +3926,9 @@ static int ps_solve_impl(hm_matrix_t h, const ps_opts* o, const void* b_dev, int
 
 int ps_solve(hm_matrix_t h, const ps_opts* o, const void* b_dev, int64_t ldb, void* x_dev,
              int64_t ldx, int32_t nrhs, ps_stats* per_rhs, void* hip_stream) {
-  return ps_solve_impl(h, o, b_dev, ldb, x_dev, ldx, nrhs, per_rhs, hip_stream, true);
+  return guarded([&] {
+    return ps_solve_impl(h, o, b_dev, ldb, x_dev, ldx, nrhs, per_rhs, hip_stream, true);
+  });
 }
 
 int hmat_export(hm_matrix_t h, const char* path) {
@@ -3921,7 +3946,7 @@ int hmat_export(hm_matrix_t h, const char* path) {
   return export_host(h->H, path, &lu, &piv);
 }
 
-int hmat_tune(hm_matrix_t h, const hm_tuning* t, void* hip_stream) {
+static int hmat_tune_impl(hm_matrix_t h, const hm_tuning* t, void* hip_stream) {
   if (!h || !t) { set_error("null argument"); return HM_EINVAL; }
   if (h->host_only) { set_error("handle was built host-only"); return HM_ESTATE; }
   if (t->mm_min_rhs < -1 || t->term_wgs < -1 || t->term_wgs > (1 << 20) ||
@@ -3957,13 +3982,17 @@ int hmat_tune(hm_matrix_t h, const hm_tuning* t, void* hip_stream) {
   int pct = h->inrow_pct;
   if (t->inrow_pct > 0) pct = t->inrow_pct;
   if (t->inrow_pct == -1) pct = 100;
-  if (wgs != h->term_wgs || pct != h->inrow_pct) {
+  if (wgs != h->term_wgs || pct != h->inrow_pct || !h->lists_ok) {
     HIPCHK(hipSetDevice(h->device));
     h->term_wgs = wgs;
     h->inrow_pct = pct;
     STCHK(build_lists(h, (hipStream_t)hip_stream));
   }
   return HM_OK;
+}
+
+int hmat_tune(hm_matrix_t h, const hm_tuning* t, void* hip_stream) {
+  return guarded([&] { return hmat_tune_impl(h, t, hip_stream); });
 }
 
 int hmat_get_tuning(hm_matrix_t h, hm_tuning* out) {
@@ -3979,8 +4008,8 @@ int hmat_get_tuning(hm_matrix_t h, hm_tuning* out) {
 
 // Times ps_solve (series kind) for every candidate tuning on zero vectors
 // of nrhs columns and keeps the fastest (median of 5 timed calls after 2).
-int hmat_autotune(hm_matrix_t h, const ps_opts* opts, int32_t nrhs, void* hip_stream,
-                  hm_tuning* best, double* best_ms) {
+static int hmat_autotune_impl(hm_matrix_t h, const ps_opts* opts, int32_t nrhs, void* hip_stream,
+                              hm_tuning* best, double* best_ms) {
   if (!h || !opts || nrhs < 1) { set_error("null argument or nrhs < 1"); return HM_EINVAL; }
   if (h->host_only) { set_error("handle was built host-only"); return HM_ESTATE; }
   HIPCHK(hipSetDevice(h->device));
@@ -4086,6 +4115,11 @@ int hmat_autotune(hm_matrix_t h, const ps_opts* opts, int32_t nrhs, void* hip_st
   return HM_OK;
 }
 
+int hmat_autotune(hm_matrix_t h, const ps_opts* opts, int32_t nrhs, void* hip_stream,
+                  hm_tuning* best, double* best_ms) {
+  return guarded([&] { return hmat_autotune_impl(h, opts, nrhs, hip_stream, best, best_ms); });
+}
+
 int hm_profile_enable(hm_matrix_t h, int32_t enable) {
   if (!h) { set_error("null handle"); return HM_EINVAL; }
   if (h->host_only) { set_error("handle was built host-only"); return HM_ESTATE; }
@@ -4154,6 +4188,13 @@ int hm_debug_gave_up(hm_matrix_t h) {
   const int32_t one = 1;
   for (int32_t* flag : {h->herr, h->mm_err})
     if (flag) HIPCHK(hipMemcpy(flag, &one, sizeof(one), hipMemcpyHostToDevice));
+  return HM_OK;
+}
+
+// The next upload of work lists (a rebuild's, or a nested solve's) fails.
+int hm_debug_fail_lists(hm_matrix_t h) {
+  if (!h || h->host_only) { set_error("no device handle"); return HM_EINVAL; }
+  h->fail_lists = true;
   return HM_OK;
 }
 

@@ -218,3 +218,4 @@ int export_host(const HostH& H, const char* path, const std::vector<cplx>* lu_ho
 
 // Not part of the public interface: for the tests.
 extern "C" int hm_debug_gave_up(hm_matrix_t h);
+extern "C" int hm_debug_fail_lists(hm_matrix_t h);
