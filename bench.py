@@ -273,7 +273,9 @@ def bench_single(a):
     log("autotune")
     tune = h.autotune(nrhs, K=wl.K, level=wl.level, precision=prec)
     log(f"autotune: {tune}")
-    mm = nrhs >= h.tuning()["mm_min_rhs"]
+    # the default threshold, 8, stands for 5 on FP64 blocks
+    mm_min = h.tuning()["mm_min_rhs"]
+    mm = nrhs >= (5 if mm_min == 8 and prec == hmps.HM_F64 else mm_min)
     # one right-hand side of a symmetric problem: the scaled series on half
     # storage when the tuning keeps it
     # one right-hand side runs on half storage where the handle has it

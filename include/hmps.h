@@ -303,8 +303,9 @@ int hmat_export(hm_matrix_t h, const char* path);
  * right-hand sides on, the term and stage-A products of ps_solve and
  * hmat_apply run as matrix-core (MFMA) contractions over tiles of 16, 32 or
  * 64 right-hand sides (FP32 blocks: three real products per complex one;
- * FP64: four); below it, one-RHS-tile streaming kernels run (default 8;
- * while it is the default, FP64 products take the matrix cores from 5 on).
+ * FP64: four); below it, one-RHS-tile streaming kernels run.  The default,
+ * 8, stands for 8 on FP32 blocks and 5 on FP64 ones; every other value holds
+ * for both.
  * term_wgs: workgroups per term launch (the work lists are split
  * evenly over them; default: compute units x resident workgroups per unit,
  * on the matrix cores a count that follows the size of the list).

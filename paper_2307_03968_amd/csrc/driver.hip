@@ -254,7 +254,6 @@ struct hm_matrix {
   int mm_multi_mode = 2;        // 1: one launch for the K terms where it applies; 2: per term
   int mm_series_wgs[2][2] = {{0, 0}, {0, 0}};  // resident round by [f32][nrhs > 16]
   int mm_min_rhs = hm::kMmMinRhsDefault;  // right-hand sides from which the MFMA kernels run
-  bool mm_min_set = false;      // mm_min_rhs was chosen by the caller or the autotuner
   int rhs_tile = 0;             // MFMA right-hand-side tile (0: by nrhs)
   int inrow_pct = 100;          // cost weight (%) of in-row rows in the work split
   // per-leaf column layout of the panels, kept to rebuild the work lists
@@ -985,12 +984,14 @@ struct Path {
 Path pick_path(const hm_matrix* h, bool f32, int nrhs) {
   // the matrix-core kernels index the row-layout vectors with 32-bit offsets
   const bool fits = (h->N + h->T + 1) * row_ld(nrhs) * (int64_t)sizeof(double2) < ((int64_t)1 << 32);
-  // FP64, threshold not chosen by the caller: the streaming kernels take four
-  // right-hand sides per panel read, so five to seven read it twice (cube 17^3,
-  // 7 RHS: 790 us a solve on them, 349 on the matrix cores; 4 RHS: 215 to 250
-  // on either).  FP32 blocks keep them up to the default threshold: they
-  // accumulate in FP64, the FP32 matrix cores do not.
-  const int min_rhs = h->mm_min_set || f32 ? h->mm_min_rhs : std::min(h->mm_min_rhs, kMmMinRhsF64);
+  // FP64 at the default threshold: the streaming kernels take four right-hand
+  // sides per panel read, so five to seven read it twice (cube 17^3, 7 RHS:
+  // 790 us a solve on them, 426 on the matrix cores; 4 RHS: 215 to 250 on
+  // either).  FP32 blocks keep them up to the default threshold: they
+  // accumulate in FP64, the FP32 matrix cores do not.  The rule follows from
+  // the threshold's value alone, so that a tuning read and written back, at
+  // once or after others, is the same tuning.
+  const int min_rhs = !f32 && h->mm_min_rhs == kMmMinRhsDefault ? kMmMinRhsF64 : h->mm_min_rhs;
   if (nrhs >= min_rhs && fits)
     return Path{true, f32 ? (const void*)h->Wmm32 : (const void*)h->Wmm64, h->groups_mm,
                 &h->sa_mm, &h->tl_series_mm, &h->tl_apply_mm, h->src_mm};
@@ -3973,7 +3974,6 @@ static int hmat_tune_impl(hm_matrix_t h, const hm_tuning* t, void* hip_stream) {
   }
   if (t->mm_min_rhs > 0) h->mm_min_rhs = t->mm_min_rhs;
   if (t->mm_min_rhs == -1) h->mm_min_rhs = kMmMinRhsDefault;
-  if (t->mm_min_rhs != 0) h->mm_min_set = t->mm_min_rhs > 0;
   if (t->rhs_tile > 0) h->rhs_tile = t->rhs_tile;
   if (t->rhs_tile == -1) h->rhs_tile = 0;
   int wgs = h->term_wgs;
@@ -4065,7 +4065,6 @@ static int hmat_autotune_impl(hm_matrix_t h, const ps_opts* opts, int32_t nrhs, 
   // the matrix-core candidates with the K terms in one launch and per term
   const int multi0 = h->mm_multi_mode;
   hm_tuning bt{h->mm_min_rhs, h->term_wgs, h->rhs_tile, h->inrow_pct, halves[0], multi0};
-  h->mm_min_set = true;
   double bms = INFINITY;
   for (int w : wgs) {
     for (int pct : pcts) {
@@ -4091,8 +4090,12 @@ static int hmat_autotune_impl(hm_matrix_t h, const ps_opts* opts, int32_t nrhs, 
               bms = ms;
               // the MFMA kernels were timed at nrhs only: they take over from
               // min(nrhs, the default threshold) on, so one right-hand side
-              // (a GEMV, far below the MFMA ridge) keeps the streaming kernels
-              bt = hm_tuning{c.mm_min == 1 ? std::min(nrhs, kMmMinRhsDefault) : nrhs + 1, w, c.tile,
+              // (a GEMV, far below the MFMA ridge) keeps the streaming kernels.
+              // Streaming kernels stay up to nrhs, past the default threshold
+              // for seven (which at that value are FP64 matrix-core products;
+              // eight read the panel twice as seven do)
+              const int above = nrhs + 1 == kMmMinRhsDefault ? nrhs + 2 : nrhs + 1;
+              bt = hm_tuning{c.mm_min == 1 ? std::min(nrhs, kMmMinRhsDefault) : above, w, c.tile,
                              pct, hs, mu};
             }
           }
