@@ -69,9 +69,9 @@ struct GroupList {
 // whatever its size (a 5,800-point handle: 7.1 ms to release in a block per
 // array, 1.5 ms so).
 struct Slabs {
+  struct Tail { char* cur; size_t left; };
   std::vector<void*> blocks;
-  char* cur = nullptr;
-  size_t left = 0;
+  std::vector<Tail> tails;  // what is left of the blocks
   Slabs() = default;
   Slabs(const Slabs&) = delete;
   Slabs& operator=(const Slabs&) = delete;
@@ -79,40 +79,39 @@ struct Slabs {
   void clear() {
     for (void* p : blocks) (void)hipFree(p);
     blocks.clear();
-    cur = nullptr;
-    left = 0;
+    tails.clear();
   }
-  // A block for the next arrays, `bytes` in all; without memory for it, and
-  // beyond it, they get blocks of their own.
+  // Room for the next arrays, `bytes` in all, with what is left of earlier
+  // blocks; without memory for it, and where an array fits no tail, it gets a
+  // block of its own.
   void reserve(size_t bytes) {
+    for (const Tail& t : tails) bytes -= std::min(bytes, t.left);
     void* b = nullptr;
-    if (bytes <= left) return;
+    if (bytes == 0) return;
     if (hipMalloc(&b, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return;
     }
-    blocks.push_back(b);
-    cur = static_cast<char*>(b);
-    left = bytes;
+    adopt(b, bytes);
   }
   // A block that served something else, for the next arrays (not zeroed).
   void adopt(void* b, size_t bytes) {
     blocks.push_back(b);
-    cur = static_cast<char*>(b);
-    left = bytes / 256 * 256;
+    tails.push_back({static_cast<char*>(b), bytes / 256 * 256});
   }
   static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 16) + 255) / 256 * 256; }
   hipError_t alloc(void** p, size_t bytes) {  // 256-byte aligned
     bytes = rounded(bytes);
-    if (bytes > left) {
-      const hipError_t e = hipMalloc(p, bytes);
-      if (e == hipSuccess) blocks.push_back(*p);
-      return e;
+    for (Tail& t : tails) {
+      if (bytes > t.left) continue;
+      *p = t.cur;
+      t.cur += bytes;
+      t.left -= bytes;
+      return hipSuccess;
     }
-    *p = cur;
-    cur += bytes;
-    left -= bytes;
-    return hipSuccess;
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) blocks.push_back(*p);
+    return e;
   }
 };
 
@@ -2042,12 +2041,13 @@ int build_lists(hm_matrix* h, hipStream_t st) {
   return HM_OK;
 }
 
-// Device bytes of a build's arrays (panels FP64 and FP32, D^{-1}-premultiplied
-// panels, LU and D^{-1}, stage-A W copies for both kernel families, in-row
-// stacks; then the half storage), from block sizes only, to within a few
-// percent; T: far coefficients.
+// Device bytes of a build's arrays, from block sizes only, to within a few
+// percent, in the order of the build: those made from the compressed far
+// factors (FP64 panels, LU, stage-A W for both kernel families, in-row
+// stacks), the rest of the panels (D^{-1}, D^{-1}-premultiplied panels, FP32
+// copies), the half storage; T: far coefficients.
 struct DataBytes {
-  int64_t panels, half, T;
+  int64_t packed, rest, half, T;
 };
 DataBytes data_bytes(const hm_matrix* h) {
   const HostH& H = h->H;
@@ -2071,13 +2071,13 @@ DataBytes data_bytes(const hm_matrix* h) {
     T += r;
   }
   const int64_t f32 = h->has_f32 ? 1 : 0;
-  const int64_t bytes =
-      16 * (P + (P - Dm)) + 32 * Dm + 2 * 16 * Wn + f32 * (8 * (2 * P - Dm) + 2 * 8 * Wn);
+  const int64_t packed = 16 * (P + Dm) + 2 * 16 * Wn;
+  const int64_t rest = 16 * P + f32 * (8 * (2 * P - Dm) + 2 * 8 * Wn);
   // half panels, their sources and v slots, the scaled far data, the
   // C^{-1}, C^{-T}, C and C^T panels and two N-vectors
   const int64_t half =
       Hn > 0 ? (16 + 8 * f32) * (Hn + Pf + Wn) + 20 * Hc + 32 * h->N + 64 * Dm : 0;
-  return {bytes, half, T};
+  return {packed, rest, half, T};
 }
 
 // One block for arrays of about `bytes` (leading dimensions are rounded up).
@@ -2143,9 +2143,47 @@ int run_gemms(const double2* A, const double2* B, double2* C, const std::vector<
 
 // Far factors the compression left on the device: per compressed block its U
 // (m x r) followed by V (n x r), until the panels, stacks and groups are packed.
+// A build that has to wait for memory keeps them on the host meanwhile.
 struct FarStore {
-  std::vector<std::unique_ptr<DevTmp<double2>>> bufs;
-  std::vector<const double2*> u;
+  struct Buf {
+    DevTmp<double2> dev;
+    size_t n = 0;
+    std::unique_ptr<char[]> host;
+  };
+  struct At { int32_t buf = -1; int64_t off = 0; };
+  std::vector<std::unique_ptr<Buf>> bufs;
+  std::vector<At> at;  // per compressed block
+  const double2* u(int b) const { return at[b].buf < 0 ? nullptr : bufs[at[b].buf]->dev.p + at[b].off; }
+  int64_t bytes() const {
+    int64_t t = 0;
+    for (const auto& b : bufs) t += (int64_t)(sizeof(double2) * b->n);
+    return t;
+  }
+  int add(size_t n) {  // a buffer of n elements, the last one
+    bufs.emplace_back(new Buf());
+    bufs.back()->n = n;
+    return bufs.back()->dev.alloc(n);
+  }
+  int to_host() {
+    for (auto& b : bufs) {
+      if (!b->dev.p) continue;
+      b->host.reset(new char[sizeof(double2) * std::max<size_t>(b->n, 1)]);
+      HIPCHK(hipMemcpy(b->host.get(), b->dev.p, sizeof(double2) * b->n, hipMemcpyDeviceToHost));
+      (void)hipFree(b->dev.p);
+      b->dev.p = nullptr;
+    }
+    return HM_OK;
+  }
+  int to_device(hipStream_t st) {
+    for (auto& b : bufs) {
+      if (b->dev.p) continue;
+      STCHK(b->dev.alloc(b->n));
+      HIPCHK(hipMemcpyAsync(b->dev.p, b->host.get(), sizeof(double2) * b->n, hipMemcpyHostToDevice, st));
+      HIPCHK(hipStreamSynchronize(st));
+      b->host.reset();
+    }
+    return HM_OK;
+  }
   // the scratch of the compression, for the handle's arrays (keep_ws): the
   // driver stalls for up to seconds where blocks are freed and allocated at
   // more than some 80 GB/s, which builds in a row do without this
@@ -2239,7 +2277,7 @@ constexpr int64_t kAcaChunkBytes = (int64_t)1 << 30;
 
 int device_aca(HostH& H, const hm_build_opts& o, FarStore& fs, hipStream_t st) {
   if (!H.aca_pending) return HM_OK;
-  fs.u.assign(H.lowrank.size(), nullptr);
+  fs.at.assign(H.lowrank.size(), FarStore::At());
   const int nb = (int)H.aca.size();
   std::vector<EntryInst> inst;
   for (const EntryParams& e : H.inst) inst.push_back({e.kind, 0, e.k, e.h});
@@ -2329,14 +2367,11 @@ int device_aca(HostH& H, const hm_build_opts& o, FarStore& fs, hipStream_t st) {
         seg.insert(seg.end(), {a.o_off + (int64_t)a.m * a.rcap, ptot + (int64_t)a.m * r, (int64_t)a.n * r});
         ptot += (int64_t)(a.m + a.n) * r;
       }
-      const double2* pk = nullptr;
       if (ptot > 0) {
-        fs.bufs.emplace_back(new DevTmp<double2>());
-        STCHK(fs.bufs.back()->alloc((size_t)ptot));
-        pk = fs.bufs.back()->p;
+        STCHK(fs.add((size_t)ptot));
         STCHK(grow(dseg, seg_cap, (int64_t)seg.size()));
         HIPCHK(hipMemcpyAsync(dseg.p, seg.data(), sizeof(int64_t) * seg.size(), hipMemcpyHostToDevice, st));
-        HIPCHK(launch_seg_copy(ws.p, fs.bufs.back()->p, dseg.p, (int)(seg.size() / 3), st));
+        HIPCHK(launch_seg_copy(ws.p, fs.bufs.back()->dev.p, dseg.p, (int)(seg.size() / 3), st));
         HIPCHK(hipStreamSynchronize(st));
       }
       for (int q = 0; q < ni; ++q) {
@@ -2353,7 +2388,7 @@ int device_aca(HostH& H, const hm_build_opts& o, FarStore& fs, hipStream_t st) {
           continue;
         }
         lr.r = res[q].rank;
-        fs.u[b] = pk + pos[q];
+        fs.at[b] = {(int32_t)fs.bufs.size() - 1, pos[q]};
       }
       b0 = b1;
     }
@@ -2382,18 +2417,17 @@ int device_aca(HostH& H, const hm_build_opts& o, FarStore& fs, hipStream_t st) {
   std::vector<std::pair<int, size_t>> rest_at;
   for (int q = 0; q < nb; ++q) {
     LowRank& lr = H.lowrank[q];
-    if (fs.u[q] || lr.r < 1) continue;
+    if (fs.at[q].buf >= 0 || lr.r < 1) continue;
     rest_at.push_back({q, rest.size()});
     for (const std::vector<cplx>* f : {&lr.U, &lr.V})
       for (const cplx& v : *f) rest.push_back(make_double2(v.real(), v.imag()));
   }
   if (!rest.empty()) {
-    fs.bufs.emplace_back(new DevTmp<double2>());
-    STCHK(fs.bufs.back()->alloc(rest.size()));
-    HIPCHK(hipMemcpyAsync(fs.bufs.back()->p, rest.data(), sizeof(double2) * rest.size(),
+    STCHK(fs.add(rest.size()));
+    HIPCHK(hipMemcpyAsync(fs.bufs.back()->dev.p, rest.data(), sizeof(double2) * rest.size(),
                           hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
-    for (const auto& ra : rest_at) fs.u[ra.first] = fs.bufs.back()->p + ra.second;
+    for (const auto& ra : rest_at) fs.at[ra.first] = {(int32_t)fs.bufs.size() - 1, (int64_t)ra.second};
   }
   H.aca_pending = false;
   std::vector<HostH::AcaBlock>().swap(H.aca);
@@ -2828,12 +2862,21 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   // device packing; otherwise it packs them itself.
   const bool dev = H.near_on_device;
   FarStore* fs = static_cast<FarStore*>(h->far_store.get());
-  if (dev && (!fs || fs->u.size() != H.lowrank.size())) {
+  if (dev && (!fs || fs->at.size() != H.lowrank.size())) {
     set_error("internal: no device factors");
     return HM_ESTATE;
   }
-  const int64_t need = data_bytes(h).panels;
-  if (dev && fs->ws.p && fs->ws_bytes <= need && fs->ws_bytes >= need / 2) {
+  // Blocks for the arrays in two steps: those packed from the far factors,
+  // then, with the factors released, the rest; so the build never holds more
+  // than the handle it ends with.  The compression's scratch serves as a block
+  // where it is of the size of the panels and, beside the factors, within that
+  // bound.
+  const DataBytes need = data_bytes(h);
+  const int64_t panels = need.packed + need.rest;
+  const bool adopted = dev && fs->ws.p && fs->ws_bytes <= panels &&
+                       fs->ws_bytes >= panels / 2 &&
+                       fs->ws_bytes + fs->bytes() <= panels + need.half;
+  if (adopted) {
     h->mem.adopt(fs->ws.p, (size_t)fs->ws_bytes);
     fs->ws.p = nullptr;
   } else {
@@ -2841,16 +2884,16 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       (void)hipFree(fs->ws.p);
       fs->ws.p = nullptr;
     }
-    reserve_data(h, need);
+    reserve_data(h, need.packed);
   }
   // U (fb.m x r) and V (fb.n x r) of far block b's orientation on the device
   auto dev_u = [&](int b) -> const double2* {
     const FarBlock& fb = H.far[b];
-    return fs->u[fb.src] + (fb.transposed ? (int64_t)fb.n * rank(b) : 0);
+    return fs->u(fb.src) + (fb.transposed ? (int64_t)fb.n * rank(b) : 0);
   };
   auto dev_v = [&](int b) -> const double2* {
     const FarBlock& fb = H.far[b];
-    return fs->u[fb.src] + (fb.transposed ? 0 : (int64_t)fb.m * rank(b));
+    return fs->u(fb.src) + (fb.transposed ? 0 : (int64_t)fb.m * rank(b));
   };
   // W_b (rank x n, times chi) at row `row` of a matrix of leading dimension ld
   auto w_item = [&](int b, int64_t at, int32_t ld) -> PackItem {
@@ -3189,6 +3232,8 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       }
     }
     STCHK(packed(&h->IR64, irtot, 0, items));
+    h->far_store.reset();  // packed: the factors leave the device
+    fs = nullptr;
   } else {
     fill_W(gsm, W);
     STCHK(upload(h, &h->Wmm64, W, st, false, kPanelPad));
@@ -3202,6 +3247,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   STCHK(upload(h, &h->ir_row0, ir_row0, st));
   STCHK(upload(h, &h->ir_soff, ir_soff, st));
   STCHK(upload(h, &h->ir_n, ir_n, st));
+  if (!adopted) reserve_data(h, need.rest);
   STCHK(dalloc(h, (void**)&h->Dinv, sizeof(double2) * std::max<int64_t>(ditot, 1) + kPanelPad));
   HIPCHK(hipMemsetAsync(h->Dinv, 0, sizeof(double2) * std::max<int64_t>(ditot, 1) + kPanelPad, st));
   STCHK(dalloc(h, (void**)&h->piv, sizeof(int32_t) * ptot));
@@ -3575,8 +3621,9 @@ static int device_part(hm_matrix* h, const hm_build_opts* opts, void* hip_stream
     h->far_store = fs;
   }
   report(opts, "packing and uploading blocks");
+  if (h->far_store)
+    STCHK(static_cast<FarStore*>(h->far_store.get())->to_device((hipStream_t)hip_stream));
   STCHK(build_device(h, opts, (hipStream_t)hip_stream));
-  h->far_store.reset();
   report(opts, "device build done");
   if (!(opts->flags & HM_BUILD_KEEP_HOST)) {
     bigvec<cplx>().swap(h->H.near_data);
@@ -4259,11 +4306,18 @@ int build_device_phase(hm_matrix_t h, const hm_build_opts* opts, void* hip_strea
   });
 }
 
+// The host part holds no device memory from here on, until the device part.
+int park_factors(hm_matrix_t h) {
+  return guarded([&]() -> int {
+    return h->far_store ? static_cast<FarStore*>(h->far_store.get())->to_host() : HM_OK;
+  });
+}
+
 // Device bytes the device part of the build will allocate, plus the workspace
 // for nrhs right-hand sides.
 int64_t device_bytes_estimate(hm_matrix_t h, int nrhs) {
   const DataBytes d = data_bytes(h);
-  return d.panels + d.half + workspace_bytes(h, nrhs, d.T);
+  return d.packed + d.rest + d.half + workspace_bytes(h, nrhs, d.T);
 }
 
 // Workspace of ensure_workspace for nrhs right-hand sides (t rows T when

@@ -196,6 +196,7 @@ void merge_hosts(std::vector<HostH>& parts, HostH& out, std::vector<int64_t>& in
 // the device part will allocate (workspace for nrhs right-hand sides
 // included), then the device part on a stream.
 int build_host_phase(const hm_problem* prob, const hm_build_opts* opts, hm_matrix_t* out);
+int park_factors(hm_matrix_t h);  // host part: its far factors leave the device for now
 int64_t device_bytes_estimate(hm_matrix_t h, int nrhs);
 int build_device_phase(hm_matrix_t h, const hm_build_opts* opts, void* hip_stream);
 int64_t workspace_bytes(hm_matrix_t h, int nrhs, int64_t T);

@@ -252,8 +252,17 @@ void hm_server::worker(int slot) {
       const int64_t need = s == HM_OK ? hm::device_bytes_estimate(h, head->nrhs) : 0;
       lk.lock();
       std::vector<hm_matrix_t> freed;
-      bool aside = false;
+      bool aside = false, parked = false;
       while (s == HM_OK && !make_room(need, key, freed)) {
+        // a build without its room holds no device memory
+        if (!parked) {
+          parked = true;
+          lk.unlock();
+          s = hm::park_factors(h);
+          if (s != HM_OK) err = hm_last_error();
+          lk.lock();
+          continue;
+        }
         // queued requests of a resident geometry that no worker runs hold
         // it in place: serve them first (they release it), keep the host part
         if (runnable_elsewhere(key)) {
