@@ -20,6 +20,12 @@
 // worker serves those requests first, since they release that geometry;
 // while other batches or builds run, the build waits for them; a geometry
 // that does not fit an idle device fails its requests with HM_ENOMEM.
+// A batch whose workspace must grow waits for the batches and builds that
+// run, not for others that wait like itself.  Once none runs, a batch whose
+// geometry holds some workspace is solved in pieces; of those that hold none
+// the oldest goes on and the others give their geometries up to it (their
+// requests return to the queue), as it does itself where only queued requests
+// of other resident geometries are in its way.  So some batch always goes on.
 // Handles freed to make room are released after the server lock is
 // dropped (a free synchronises the device).
 #include <hip/hip_runtime.h>
@@ -60,6 +66,8 @@ struct Geometry {
   bool building = false;
   bool reserved = false; // building, with its device bytes counted
   bool busy = false;     // a worker runs a batch on it
+  hm_ticket_t waiting = 0;  // its batch waits for room: the oldest request (0: no)
+  bool give_up = false;  // its waiting batch returns to the queue, the handle goes
   bool wait_room = false;  // a cold build stepped aside until room frees up
   hm_matrix_t staged = nullptr;  // its host part, kept meanwhile
   int pending = 0;       // queued + running requests
@@ -122,12 +130,21 @@ struct hm_server {
         return true;
     return false;
   }
-  // with mu held: batches or builds (with their room) running elsewhere
-  bool running_elsewhere(uint64_t except) const {
+  // with mu held: batches or builds (with their room) running elsewhere;
+  // waiting: batches that wait for room count too (they end without a build)
+  bool running_elsewhere(uint64_t except, bool waiting) const {
     for (auto& kv : geoms)
-      if (kv.first != except && (kv.second.busy || kv.second.reserved)) return true;
+      if (kv.first != except &&
+          ((kv.second.busy && (waiting || !kv.second.waiting)) || kv.second.reserved))
+        return true;
     return false;
   }
+  // Room for `extra` more bytes of a batch on geometry `key`, whose oldest
+  // request is `id`; lk (on mu) held, released while it waits.  chunked: the
+  // geometry holds workspace for a narrower piece already.
+  enum Room { kRoom, kNoRoom, kGiveUp };
+  Room wait_room(int64_t extra, uint64_t key, hm_ticket_t id, bool chunked,
+                 std::vector<hm_matrix_t>& freed, std::unique_lock<std::mutex>& lk);
   void finish(std::vector<Request*>& batch, int status, const std::string& err);
 };
 
@@ -153,6 +170,55 @@ bool hm_server::make_room(int64_t need, uint64_t except, std::vector<hm_matrix_t
     st.evictions++;
   }
   return true;
+}
+
+hm_server::Room hm_server::wait_room(int64_t extra, uint64_t key, hm_ticket_t id, bool chunked,
+                                     std::vector<hm_matrix_t>& freed,
+                                     std::unique_lock<std::mutex>& lk) {
+  Geometry& g = geoms[key];
+  Room r = kRoom;
+  while (!make_room(extra, key, freed)) {
+    if (g.give_up) {
+      r = kGiveUp;
+      break;
+    }
+    bool tell = !g.waiting;  // the others look again: this batch runs no longer
+    if (!running_elsewhere(key, false)) {
+      if (chunked) {
+        r = kNoRoom;
+        break;
+      }
+      Geometry* other = nullptr;  // the youngest other batch that waits
+      bool oldest = true;
+      for (auto& kv : geoms) {
+        Geometry& o = kv.second;
+        if (kv.first == key || !o.waiting) continue;
+        oldest = oldest && id < o.waiting;
+        if (!other || o.waiting > other->waiting) other = &o;
+      }
+      if (!other) {
+        // queued requests of a resident geometry without a worker hold it in
+        // place: this worker serves them first
+        r = runnable_elsewhere(key) ? kGiveUp : kNoRoom;
+        break;
+      }
+      if (oldest && !other->give_up) other->give_up = tell = true;
+    }
+    g.waiting = id;
+    if (tell) cv.notify_all();
+    if (!freed.empty()) {  // what was evicted so far is released, not held
+      std::vector<hm_matrix_t> gone;
+      gone.swap(freed);
+      lk.unlock();
+      for (hm_matrix_t f : gone) hmat_free(f);
+      lk.lock();
+      continue;
+    }
+    cv.wait(lk);
+  }
+  g.waiting = 0;
+  g.give_up = false;
+  return r;
 }
 
 void hm_server::finish(std::vector<Request*>& batch, int status, const std::string& err) {
@@ -271,7 +337,7 @@ void hm_server::worker(int slot) {
         }
         // else wait only for work that will end without this worker:
         // running batches and builds that already hold their room
-        if (!running_elsewhere(key)) {
+        if (!running_elsewhere(key, true)) {
           s = HM_ENOMEM;
           err = "geometry needs about " + std::to_string(need) +
                 " device bytes, more than the budget allows";
@@ -353,8 +419,6 @@ void hm_server::worker(int slot) {
     g.busy = true;
     hm_matrix_t h = g.h;
     const int64_t n = g.n;
-    st.batches++;
-    st.batch_rhs += cols;
     // a wider batch than before grows the geometry's workspace: room first.
     // When no room can be made (the other resident geometries hold queued
     // work and nothing runs that would release memory), the batch is solved
@@ -363,44 +427,55 @@ void hm_server::worker(int slot) {
     std::string err;
     std::vector<hm_matrix_t> freed;
     int chunk = cols;
+    Room room = kRoom;
     if (cols > hm::workspace_rhs(h)) {
       const int64_t extra = hm::workspace_bytes(h, cols, 0) - hm::workspace_bytes(h, hm::workspace_rhs(h), 0);
-      bool grown = true;
-      while (!make_room(extra, key, freed)) {
-        if (!running_elsewhere(key)) {
-          grown = false;
-          if (hm::workspace_rhs(h) >= 1) {
-            chunk = hm::workspace_rhs(h);
-          } else {
-            s = HM_ENOMEM;
-            err = "workspace for " + std::to_string(cols) + " right-hand sides exceeds the budget";
-          }
-          break;
-        }
-        cv.wait(lk);
+      room = wait_room(extra, key, head->id, hm::workspace_rhs(h) >= 1, freed, lk);
+      if (room == kRoom) {
+        g.bytes += extra;
+      } else if (hm::workspace_rhs(h) >= 1) {
+        chunk = hm::workspace_rhs(h);
+      } else {
+        s = HM_ENOMEM;
+        err = "workspace for " + std::to_string(cols) + " right-hand sides exceeds the budget";
       }
-      if (grown) g.bytes += extra;
     }
     // GMRES keeps its basis on the handle: room for its growth too
-    if (s == HM_OK && o.kind == PS_GMRES) {
+    if (s == HM_OK && room != kGiveUp && o.kind == PS_GMRES) {
       const int m = hm::gmres_restart(o);
       const int64_t extra = hm::gmres_growth_bytes(h, m, chunk);
-      bool grown = true;
-      while (extra > 0 && !make_room(extra, key, freed)) {
-        if (!running_elsewhere(key)) {
-          grown = false;
-          if (hm::gmres_rhs(h, m) >= 1) {
-            chunk = std::min(chunk, hm::gmres_rhs(h, m));
-          } else {
-            s = HM_ENOMEM;
-            err = "GMRES workspace for " + std::to_string(cols) + " right-hand sides exceeds the budget";
-          }
-          break;
+      if (extra > 0) {
+        room = wait_room(extra, key, head->id, hm::gmres_rhs(h, m) >= 1, freed, lk);
+        if (room == kRoom) {
+          g.bytes += extra;
+        } else if (hm::gmres_rhs(h, m) >= 1) {
+          chunk = std::min(chunk, hm::gmres_rhs(h, m));
+        } else {
+          s = HM_ENOMEM;
+          err = "GMRES workspace for " + std::to_string(cols) + " right-hand sides exceeds the budget";
         }
-        cv.wait(lk);
       }
-      if (grown) g.bytes += extra;
     }
+    if (room == kGiveUp) {
+      // back to the queue, in order; the geometry is built again for them
+      for (auto r = batch.rbegin(); r != batch.rend(); ++r) {
+        (*r)->state = PS_QUEUED;
+        auto at = std::find_if(queue.begin(), queue.end(), [&](Request* q) { return q->id > (*r)->id; });
+        queue.insert(at, *r);
+      }
+      freed.push_back(h);
+      g.h = nullptr;
+      g.bytes = 0;
+      g.busy = false;
+      st.evictions++;
+      lk.unlock();
+      for (hm_matrix_t f : freed) hmat_free(f);
+      lk.lock();
+      cv.notify_all();
+      continue;
+    }
+    st.batches++;
+    st.batch_rhs += cols;
     if (chunk < cols) st.split_batches++;
     lk.unlock();
     for (hm_matrix_t f : freed) hmat_free(f);
