@@ -72,6 +72,7 @@ struct Slabs {
   struct Tail { char* cur; size_t left; };
   std::vector<void*> blocks;
   std::vector<Tail> tails;  // what is left of the blocks
+  int64_t bytes = 0;        // of the blocks, whole
   Slabs() = default;
   Slabs(const Slabs&) = delete;
   Slabs& operator=(const Slabs&) = delete;
@@ -80,37 +81,42 @@ struct Slabs {
     for (void* p : blocks) (void)hipFree(p);
     blocks.clear();
     tails.clear();
+    bytes = 0;
   }
   // Room for the next arrays, `bytes` in all, with what is left of earlier
   // blocks; without memory for it, and where an array fits no tail, it gets a
   // block of its own.
-  void reserve(size_t bytes) {
-    for (const Tail& t : tails) bytes -= std::min(bytes, t.left);
+  void reserve(size_t size) {
+    for (const Tail& t : tails) size -= std::min(size, t.left);
     void* b = nullptr;
-    if (bytes == 0) return;
-    if (hipMalloc(&b, bytes) != hipSuccess) {
+    if (size == 0) return;
+    if (hipMalloc(&b, size) != hipSuccess) {
       (void)hipGetLastError();
       return;
     }
-    adopt(b, bytes);
+    adopt(b, size);
   }
   // A block that served something else, for the next arrays (not zeroed).
-  void adopt(void* b, size_t bytes) {
+  void adopt(void* b, size_t size) {
+    own(b, size);
+    tails.push_back({static_cast<char*>(b), size / 256 * 256});
+  }
+  void own(void* b, size_t size) {  // a block in use
     blocks.push_back(b);
-    tails.push_back({static_cast<char*>(b), bytes / 256 * 256});
+    bytes += (int64_t)size;
   }
   static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 16) + 255) / 256 * 256; }
-  hipError_t alloc(void** p, size_t bytes) {  // 256-byte aligned
-    bytes = rounded(bytes);
+  hipError_t alloc(void** p, size_t size) {  // 256-byte aligned
+    size = rounded(size);
     for (Tail& t : tails) {
-      if (bytes > t.left) continue;
+      if (size > t.left) continue;
       *p = t.cur;
-      t.cur += bytes;
-      t.left -= bytes;
+      t.cur += size;
+      t.left -= size;
       return hipSuccess;
     }
-    const hipError_t e = hipMalloc(p, bytes);
-    if (e == hipSuccess) blocks.push_back(*p);
+    const hipError_t e = hipMalloc(p, size);
+    if (e == hipSuccess) own(*p, size);
     return e;
   }
 };
@@ -135,7 +141,6 @@ struct hm_matrix {
   int ninst = 1;
   std::vector<int64_t> inst_off;
   double build_ms = 0;
-  int64_t bytes = 0;
   Slabs mem;  // the handle's device arrays
   UploadBatch* batch = nullptr;  // open while a build or a list rebuild runs
 
@@ -261,7 +266,6 @@ struct hm_matrix {
   std::vector<int32_t> ir_ncol_h;
   std::vector<std::vector<int64_t>> ir_end, gl_end;
   Slabs list_mem;  // device work lists (rebuilt by hmat_tune)
-  int64_t list_bytes = 0;
   bool lists_ok = false;   // false while, and after, a rebuild that failed
   bool fail_lists = false; // tests: the next upload of work lists fails
   int64_t partial_rows = 0;     // partial rows of the streaming lists, a column per right-hand side
@@ -275,7 +279,6 @@ struct hm_matrix {
   int32_t* counters = nullptr;  // workspace
   // workspace
   int ws_nrhs = 0;
-  int64_t ws_bytes = 0;
   double2 *xin0 = nullptr, *xin1 = nullptr, *xt = nullptr, *bt = nullptr, *rt = nullptr,
           *dt = nullptr, *partial = nullptr;
   // [y | t] in row layout for the matrix-core kernels (ld ws_ldr): FP64 and
@@ -343,8 +346,6 @@ int dalloc(hm_matrix* h, void** p, size_t bytes, bool lists = false) {
     set_error("hipMalloc of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e));
     return HM_ENOMEM;
   }
-  h->bytes += (int64_t)bytes;
-  if (lists) h->list_bytes += (int64_t)bytes;
   return HM_OK;
 }
 
@@ -823,7 +824,6 @@ int ensure_workspace(hm_matrix* h, int nrhs, hipStream_t st) {
   if (nrhs <= h->ws_nrhs) return HM_OK;
   h->ws_mem.clear();
   h->ws_nrhs = 0;
-  h->ws_bytes = 0;
   const int64_t ldin = h->N + h->T;
   auto al = [&](void** p, size_t bytes) -> int {
     hipError_t e = h->ws_mem.alloc(p, bytes);
@@ -832,7 +832,6 @@ int ensure_workspace(hm_matrix* h, int nrhs, hipStream_t st) {
       set_error("workspace hipMalloc failed: " + std::string(hipGetErrorString(e)));
       return HM_ENOMEM;
     }
-    h->ws_bytes += (int64_t)std::max<size_t>(bytes, 16);
     return HM_OK;
   };
   const int64_t ldr = row_ld(nrhs);
@@ -1969,8 +1968,6 @@ int build_lists(hm_matrix* h, hipStream_t st) {
   const int ws_nrhs = h->ws_nrhs;
   h->ws_nrhs = 0;
   h->list_mem.clear();
-  h->bytes -= h->list_bytes;
-  h->list_bytes = 0;
   const int64_t old_rows = h->partial_rows, old_half = h->partial_rows_half, old_mm = h->partial_rows_mm;
   h->partial_rows = h->partial_rows_half = h->partial_rows_mm = 0;
   const HostH& H = h->H;
@@ -2777,9 +2774,8 @@ int build_half(hm_matrix* h, const HalfSrc& hs, hipStream_t st) {
   h->CHT = cht;
   h->CF = cf;
   h->CFT = cft;
-  h->mem.blocks.push_back(cpan.p);
+  h->mem.own(cpan.p, 4 * sizeof(double2) * (size_t)chld);
   cpan.p = nullptr;
-  h->bytes += 4 * (int64_t)sizeof(double2) * chld;
   STCHK(dalloc(h, (void**)&h->hwork, sizeof(double2) * h->N));
   if (h->has_f32) {
     const int64_t n_ir = std::max<int64_t>(irtot, 1), n_w = std::max<int64_t>(wtot, 1);
@@ -3435,7 +3431,7 @@ void fill_info(const hm_matrix* h, hm_info* out) {
     out->far_rank_sum[fb.level] += r;
     out->far_entries[fb.level] += (int64_t)r * (fb.m + fb.n);
   }
-  out->device_bytes = h->bytes;
+  out->device_bytes = h->mem.bytes + h->list_mem.bytes;
   out->build_ms = h->build_ms;
   out->num_instances = h->ninst;
   for (int li = 0; li < (int)h->ent_M.size(); ++li) {
@@ -4354,7 +4350,9 @@ int64_t gmres_growth_bytes(hm_matrix_t h, int m, int nrhs) {
 
 int gmres_rhs(hm_matrix_t h, int m) { return m <= h->gm_m ? h->gm_nrhs : 0; }
 
-int64_t resident_bytes(hm_matrix_t h) { return h->bytes + h->ws_bytes; }
+int64_t resident_bytes(hm_matrix_t h) {
+  return h->mem.bytes + h->list_mem.bytes + h->ws_mem.bytes + h->gm_mem.bytes;
+}
 
 int64_t matrix_n(hm_matrix_t h) { return h->N; }
 

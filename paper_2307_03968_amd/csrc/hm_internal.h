@@ -201,7 +201,9 @@ int64_t device_bytes_estimate(hm_matrix_t h, int nrhs);
 int build_device_phase(hm_matrix_t h, const hm_build_opts* opts, void* hip_stream);
 int64_t workspace_bytes(hm_matrix_t h, int nrhs, int64_t T);
 int workspace_rhs(hm_matrix_t h);        // right-hand sides the workspace holds
-int64_t resident_bytes(hm_matrix_t h);  // device blocks + workspace
+// device memory of the handle, whole blocks: arrays, work lists, workspace,
+// GMRES basis
+int64_t resident_bytes(hm_matrix_t h);
 constexpr int kMmMinRhsDefault = 8;  // default right-hand sides from which MFMA kernels run
 constexpr int kMmMinRhsF64 = 5;      // the same for FP64 blocks when the threshold is the default
 // GMRES (PS_GMRES): the cycle length a call with these options uses, and the

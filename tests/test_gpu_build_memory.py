@@ -49,7 +49,30 @@ def test_build_peak_is_the_handle(make, leaf, tol, flags):
     first = [m for m, _ in marks].index("panels packed and uploaded")
     for m, u in marks[first:]:
         assert u <= end + 8 * MB, (m, u, end)
+    # what the handle says it holds is what the device has given out (blocks
+    # come in 2 MB pages)
+    held = h.info()["device_bytes"]
+    assert abs(held - end) <= 24 * MB, (held, end)
     h.close()
+
+
+def test_server_resident_bytes_are_what_the_device_gave_out():
+    """Workspace and GMRES basis (32 right-hand sides: 96 and 192 MB) included."""
+    srv = hmps.Server(slots=1)
+
+    def requests(key, n):
+        p = W.sphere_problem(n, math.sqrt(n / 1536))
+        B = W.plane_waves(p.xyz, W.directions(32, 3))
+        print(f"[gpu-case] server resident bytes, {n} points", flush=True)
+        srv.wait(srv.submit(key, B, K=2, prob=p, leaf_max=64))
+        srv.wait(srv.submit(key, B, K=0, kind=hmps.PS_GMRES, max_passes=4, refine_tol=1e-9))
+        return _used(), srv.info()["resident_bytes"]
+
+    u0, r0 = requests(1, 600)  # what the kernels' queues need is there from now on
+    u1, r1 = requests(2, 6000)
+    print(f"[gpu-case]   used {(u1 - u0) / MB:.1f} MB, resident {(r1 - r0) / MB:.1f} MB", flush=True)
+    assert abs((u1 - u0) - (r1 - r0)) <= 32 * MB
+    srv.close()
 
 
 def test_server_build_waiting_for_room_holds_no_device_memory():
