@@ -453,6 +453,15 @@ int mm_units(const hm_matrix* h, int64_t total, bool dinv) {
   return (int)std::max<int64_t>(8, u / 8 * 8);
 }
 
+// Columns of a matrix-core piece of such a list, at most (make_termlist).
+int64_t mm_piece_cols(const hm_matrix* h, int64_t total) {
+  if (h->max_m <= 96) return kMmMaxCols;
+  return std::max<int64_t>(256, std::min<int64_t>(kMmMaxCols, total / (768 * h->max_m)));
+}
+
+// Half-panel columns and far pairs of a half-list piece, at least.
+constexpr int64_t kMinHalfCols = 96, kMinHalfPairs = 2;
+
 // First far blocks of a half list that holds those of one level only (and no
 // half-panel columns): in-row stack rows and far pairs per leaf.
 struct FarFirst {
@@ -508,9 +517,7 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
   // per CU) take FP64 products instead (sphere 6,000, 64 RHS: 4.3e-8 in 450 us
   // a solve; FP32 sums 1.8e-7 in 300); leaves whose waves do not split the
   // columns keep their pieces at a 768th of the list.
-  const int64_t mm_cols =
-      h->max_m <= 96 ? kMmMaxCols
-                     : std::max<int64_t>(256, std::min<int64_t>(kMmMaxCols, total / (768 * h->max_m)));
+  const int64_t mm_cols = mm_piece_cols(h, total);
   tl.fp64_sums = mm && total < mm_two_per_cu(h);
   std::vector<TermItem> items;
   std::vector<int32_t> wg_of, vleaf, lcnt(hl ? h->nl : 0, 0);
@@ -534,9 +541,9 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     int64_t ncols = 0, npair = 0;
     for (const Seg& sg : segs) (sg.kind == 2 ? ncols : npair) += sg.kind >= 2 ? sg.u1 - sg.u0 : 0;
     const int64_t half_cols =
-        std::max<int64_t>(96, std::min<int64_t>(kHalfPieceCols, (ncols / 700 + 31) / 32 * 32));
+        std::max(kMinHalfCols, std::min<int64_t>(kHalfPieceCols, (ncols / 700 + 31) / 32 * 32));
     const bool eights = npair >= 3584 || (half_cols >= 224 && npair >= 1024 && npair < 2048);
-    const int64_t half_pairs = eights ? kHalfPiecePairs : (npair > 512 ? 4 : 2);
+    const int64_t half_pairs = eights ? kHalfPiecePairs : (npair > 512 ? 4 : kMinHalfPairs);
     for (const Seg& sg : segs) {
       const int m = h->H.leaf_size[sg.leaf];
       int64_t u = sg.u0;
@@ -2042,17 +2049,21 @@ int build_lists(hm_matrix* h, hipStream_t st) {
 // percent, in the order of the build: those made from the compressed far
 // factors (FP64 panels, LU, stage-A W for both kernel families, in-row
 // stacks), the rest of the panels (D^{-1}, D^{-1}-premultiplied panels, FP32
-// copies), the half storage; T: far coefficients.
+// copies), the half storage; the sources of the panel columns; T: far
+// coefficients.
 struct DataBytes {
-  int64_t packed, rest, half, T;
+  int64_t packed, rest, half, sources, T;
 };
 DataBytes data_bytes(const hm_matrix* h) {
   const HostH& H = h->H;
   int64_t P = 0, Dm = 0, Wn = 0, T = 0, Hn = 0, Hc = 0;
-  const bool sym = h->want_half;  // half panels (surface, and volume on Z diag(1/chi))
+  // half panels (surface, and volume on Z diag(1/chi))
+  const bool sym = h->want_half && h->max_m <= kHalfMaxLeaf && h->max_m <= kCsymMaxLeaf;
+  int64_t cols = 0;
   for (const NearBlock& nb : H.near) {
     const int64_t m = even_ld(H.leaf_size[nb.t_leaf]);
     P += m * H.leaf_size[nb.s_leaf];
+    cols += H.leaf_size[nb.s_leaf];
     if (nb.t_leaf == nb.s_leaf) Dm += (int64_t)H.leaf_size[nb.t_leaf] * H.leaf_size[nb.t_leaf];
     if (sym && nb.t_leaf < nb.s_leaf) {
       Hn += m * H.leaf_size[nb.s_leaf];
@@ -2066,6 +2077,7 @@ DataBytes data_bytes(const hm_matrix* h) {
     Pf += r * fb.m;
     Wn += r * fb.n;
     T += r;
+    cols += r * (H.tree.leaf_of[fb.t_off + fb.m - 1] - H.tree.leaf_of[fb.t_off] + 1);
   }
   const int64_t f32 = h->has_f32 ? 1 : 0;
   const int64_t packed = 16 * (P + Dm) + 2 * 16 * Wn;
@@ -2074,12 +2086,16 @@ DataBytes data_bytes(const hm_matrix* h) {
   // C^{-1}, C^{-T}, C and C^T panels and two N-vectors
   const int64_t half =
       Hn > 0 ? (16 + 8 * f32) * (Hn + Pf + Wn) + 20 * Hc + 32 * h->N + 64 * Dm : 0;
-  return {packed, rest, half, T};
+  return {packed, rest, half, 8 * cols, T};
 }
 
-// One block for arrays of about `bytes` (leading dimensions are rounded up).
+// One block for arrays of about `bytes` (leading dimensions are rounded up,
+// small arrays fill the tail).
+int64_t block_bytes(int64_t bytes) {
+  return bytes > 0 ? bytes + bytes / 100 + std::min<int64_t>(bytes / 16, (int64_t)1 << 20) : 0;
+}
 void reserve_data(hm_matrix* h, int64_t bytes) {
-  if (bytes > 0) h->mem.reserve((size_t)(bytes + bytes / 100) + ((size_t)1 << 20));
+  if (bytes > 0) h->mem.reserve((size_t)block_bytes(bytes));
 }
 
 // Host layout of the far-field device arrays the half-storage data is
@@ -4309,28 +4325,56 @@ int park_factors(hm_matrix_t h) {
   });
 }
 
-// Device bytes the device part of the build will allocate, plus the workspace
-// for nrhs right-hand sides.
+// Device bytes the device part of the build will allocate (its blocks, the
+// sources, and up to 512 KB of small arrays that fit no tail), plus the
+// workspace for nrhs right-hand sides.  Spheres and cubes of 300 to 24,576
+// points, 1 to 64 right-hand sides: from 0.999 to 1.05 of what is allocated.
 int64_t device_bytes_estimate(hm_matrix_t h, int nrhs) {
   const DataBytes d = data_bytes(h);
-  return d.packed + d.rest + d.half + workspace_bytes(h, nrhs, d.T);
+  const int64_t blocks = block_bytes(d.packed) + block_bytes(d.rest) + block_bytes(d.half);
+  return blocks + std::min<int64_t>(blocks / 100, (int64_t)512 << 10) + d.sources +
+         workspace_bytes(h, nrhs, d.T);
+}
+
+// At least partial_entries(h, nrhs), before the lists exist.  A piece starts
+// where a segment of its leaf does, where a unit or workgroup does, or where
+// the piece before it reached its largest size (make_termlist); half lists add
+// the v slots and the rows of the far pairs.
+static int64_t partial_bound(const hm_matrix* h, int nrhs) {
+  const HostH& H = h->H;
+  int64_t total = 0, inrow = 0, hcols = 0, hent = 0, hblk = 0, pair = 0;
+  for (const NearBlock& nb : H.near) {
+    const int64_t m = H.leaf_size[nb.t_leaf], n = H.leaf_size[nb.s_leaf];
+    total += m * n;
+    if (nb.t_leaf >= nb.s_leaf) continue;
+    hcols += n;
+    hent += m * n;
+    hblk += m;
+  }
+  for (const FarBlock& fb : H.far) {
+    const int64_t r = H.lowrank[fb.src].r;
+    total += r * fb.m;
+    const int a = H.tree.leaf_of[fb.t_off];
+    if (H.leaf_off[a] != fb.t_off || H.leaf_size[a] != fb.m) continue;  // a global block
+    inrow += r * fb.m;
+    if (fb.t_off < fb.s_off) pair += fb.m / kMinHalfPairs + fb.n;
+  }
+  const int64_t stream = 3 * h->N + (int64_t)h->term_wgs * h->max_m + inrow / kInRowTile;
+  const int64_t mm = 2 * h->N + (int64_t)mm_units(h, total, false) * h->max_m + total / mm_piece_cols(h, total);
+  const int64_t half = h->want_half && h->max_m <= kHalfMaxLeaf
+                           ? 4 * h->N + hent / kMinHalfCols + hblk / kMaxVLeaves + hcols + pair +
+                                 inrow / kHalfInRowTile + total / kHalfChunk
+                           : 0;
+  return std::max({stream * nrhs, half, mm * row_ld(nrhs)});
 }
 
 // Workspace of ensure_workspace for nrhs right-hand sides (t rows T when
 // the device part is not built yet, else the handle's own).
 int64_t workspace_bytes(hm_matrix_t h, int nrhs, int64_t T) {
-  if (h->device >= 0) T = h->T;
+  const bool built = h->partial_rows > 0;
+  if (built) T = h->T;
   const int64_t ldr = row_ld(nrhs);
-  int64_t partial = partial_entries(h, nrhs);
-  if (h->partial_rows == 0) {
-    // not built yet: every piece of a list is a leaf's first or a unit's first
-    int64_t total = 0;
-    for (const NearBlock& nb : h->H.near)
-      total += (int64_t)h->H.leaf_size[nb.t_leaf] * h->H.leaf_size[nb.s_leaf];
-    for (const FarBlock& fb : h->H.far) total += (int64_t)h->H.lowrank[fb.src].r * fb.m;
-    partial = std::max(nrhs * (h->N + (int64_t)h->term_wgs * h->max_m),
-                       ldr * (h->N + (int64_t)mm_units(h, total, false) * h->max_m));
-  }
+  const int64_t partial = built ? partial_entries(h, nrhs) : partial_bound(h, nrhs);
   const int64_t items = h->n_norm_items > 0 ? h->n_norm_items : h->N / kNormRows + 1;
   return (int64_t)nrhs * (16 * 2 * (h->N + T) + 16 * 4 * h->N + 16 * (items + h->nseg)) +
          ldr * 24 * 2 * (h->N + T) + 16 * partial + 4 * counter_count(h, nrhs);

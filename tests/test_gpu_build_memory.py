@@ -75,6 +75,42 @@ def test_server_resident_bytes_are_what_the_device_gave_out():
     srv.close()
 
 
+@pytest.mark.parametrize("make, leaf, tol", [
+    (lambda: W.sphere_problem(6000, math.sqrt(6000 / 1536)), 64, 1e-4),
+    (lambda: W.sphere_problem(24576, 4.0), 128, 1e-4),
+    (lambda: W.cube_problem(17, 17 / 16), 128, 1e-5),
+], ids=["leaf_64", "leaf_128", "volume"])
+def test_server_builds_what_it_can_serve(make, leaf, tol):
+    """Around the budget that a geometry and its first batch need, a server
+    either serves the batch or refuses it before the build; a twentieth more is
+    enough."""
+    prob = make()
+    B = W.plane_waves(prob.xyz, W.directions(64, 3))
+    staging = 2 * 16 * 64 * prob.n  # of the worker
+
+    def serve(budget):
+        srv = hmps.Server(budget_bytes=budget, slots=1)
+        err = None
+        try:
+            srv.wait(srv.submit(1, B, K=1, prob=prob, leaf_max=leaf, aca_tol=tol))
+        except hmps.HmpsError as e:
+            err = str(e)
+        i = srv.info()
+        srv.close()
+        return err, i
+
+    need = serve(0)[1]["resident_bytes"] - staging
+    got = []
+    for pct in range(90, 104):
+        budget = need * pct // 100
+        print(f"[gpu-case] n={prob.n}, {pct}% of the bytes needed", flush=True)
+        err, i = serve(budget)
+        got.append((pct, err, i["builds"]))
+        assert (i["builds"] == 1 and i["resident_bytes"] <= budget + staging) if err is None else i["builds"] == 0, got[-1]
+    assert got[0][1] is not None
+    assert serve(need * 105 // 100)[0] is None
+
+
 def test_server_build_waiting_for_room_holds_no_device_memory():
     """One worker: geometry 2's build has no room while geometry 1 has queued
     requests, so it steps aside; while they run, the device holds geometry 1."""
