@@ -527,23 +527,29 @@ int make_termlist(hm_matrix* h, const std::vector<std::vector<std::pair<int64_t,
     // piece from a queue): pieces of bounded size, largest estimated cost
     // first so that the last pieces taken are small.
     std::vector<std::pair<int64_t, TermItem>> pcs;
-    // Piece sizes by the size of the list.  Wide pieces cost the least per byte,
-    // but a short list then leaves workgroups idle and every term waits for its
-    // last piece: about 700 half-panel pieces of 96 to kHalfPieceCols columns.
-    // Far pairs come in fours (one per wave) or, in short lists, twos; eights
-    // (kHalfPiecePairs) where the list is long, or of middle length beside wide
-    // half-panel pieces.  Four terms, FP64 / FP32, us, pieces of 256 columns and
-    // 8 pairs against this rule: sphere 1,536 133/135 -> 82/80, 6,000 195/167 ->
-    // 150/138, 9,358 251/211 -> 230/177, 16,000 368/273 both, 24,576 415/290 ->
-    // 406/286; cube 17^3 275/254 -> 229/183, 22^3 451/347 -> 439/313, 31^3
-    // 1,955/1,283 both (fours cost it 2,027/1,326; 1,400 pieces cost 16,000
-    // points 417/313).
+    // Piece sizes by what the list holds for each resident workgroup.  Wide
+    // pieces cost the least per byte, but in a short list some workgroups then
+    // get none, and every term waits for its last piece.
+    //   Half-panel columns: about 1.6 pieces a workgroup, of 96 to
+    //   kHalfPieceCols columns.
+    //   Far pairs: fours, one per wave, from one pair a workgroup on; twos
+    //   below; eights (kHalfPiecePairs: half the tickets, items and sums) from
+    //   six pairs a workgroup on, where a term still has pieces to spare.
+    // Four terms, FP64 / FP32, us.  Pieces of 256 columns and 8 pairs against
+    // this rule (leaves of at most 64 rows, then 128): sphere 1,536 133/134 ->
+    // 85/83, 6,000 195/166 -> 151/138, 14,000 256/205 -> 240/200; 9,358 255/212
+    // -> 219/178; cube 16^3 202/175 -> 139/114, 17^3 278/255 -> 223/183.
+    // Columns: 14,000 points 237 with 192, 253 with 224; 16,384 points (128
+    // rows) 347 with 256, 384 with 128.  Pairs, per workgroup: 0.3 (1,536
+    // points) 85 in twos, 98 in fours; 1.6 (cube 20^3) 328 and 312; 5.7 (24,576
+    // points) 412 in fours, 418 in eights; 6.0 (16,384) 354 and 347; 30 (cube
+    // 32^3) 1,544 and 1,496.
     int64_t ncols = 0, npair = 0;
     for (const Seg& sg : segs) (sg.kind == 2 ? ncols : npair) += sg.kind >= 2 ? sg.u1 - sg.u0 : 0;
+    const int64_t wgs = h->half_wgs_multi;
     const int64_t half_cols =
-        std::max(kMinHalfCols, std::min<int64_t>(kHalfPieceCols, (ncols / 700 + 31) / 32 * 32));
-    const bool eights = npair >= 3584 || (half_cols >= 224 && npair >= 1024 && npair < 2048);
-    const int64_t half_pairs = eights ? kHalfPiecePairs : (npair > 512 ? 4 : kMinHalfPairs);
+        std::max(kMinHalfCols, std::min<int64_t>(kHalfPieceCols, (5 * ncols / (8 * wgs) + 31) / 32 * 32));
+    const int64_t half_pairs = npair >= 6 * wgs ? kHalfPiecePairs : (npair > wgs ? 4 : kMinHalfPairs);
     for (const Seg& sg : segs) {
       const int m = h->H.leaf_size[sg.leaf];
       int64_t u = sg.u0;
