@@ -2055,10 +2055,17 @@ int build_lists(hm_matrix* h, hipStream_t st) {
 // percent, in the order of the build: those made from the compressed far
 // factors (FP64 panels, LU, stage-A W for both kernel families, in-row
 // stacks), the rest of the panels (D^{-1}, D^{-1}-premultiplied panels, FP32
-// copies), the half storage; the sources of the panel columns; T: far
-// coefficients.
+// copies), the half storage; the far factors themselves, which a build holds
+// until they are packed; the sources of the panel columns; T: far coefficients.
 struct DataBytes {
-  int64_t packed, rest, half, sources, T;
+  int64_t packed, rest, half, far, sources, T;
+  // The rest of the panels gets its block once the factors are gone where the
+  // half storage would not take their room later anyway, so that a build never
+  // holds more than the handle it ends with.  One block for all panels
+  // otherwise: the driver takes 0.25 ms for every 64 MB or so it is given back
+  // and as much for a larger block whole (1,500 points: build, solve and release
+  // 4.3 ms with two blocks, 3.9 with one).
+  bool two_blocks() const { return far > half; }
 };
 DataBytes data_bytes(const hm_matrix* h) {
   const HostH& H = h->H;
@@ -2092,7 +2099,7 @@ DataBytes data_bytes(const hm_matrix* h) {
   // C^{-1}, C^{-T}, C and C^T panels and two N-vectors
   const int64_t half =
       Hn > 0 ? (16 + 8 * f32) * (Hn + Pf + Wn) + 20 * Hc + 32 * h->N + 64 * Dm : 0;
-  return {packed, rest, half, 8 * cols, T};
+  return {packed, rest, half, 16 * Pf, 8 * cols, T};
 }
 
 // One block for arrays of about `bytes` (leading dimensions are rounded up,
@@ -2884,11 +2891,9 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
     set_error("internal: no device factors");
     return HM_ESTATE;
   }
-  // Blocks for the arrays in two steps: those packed from the far factors,
-  // then, with the factors released, the rest; so the build never holds more
-  // than the handle it ends with.  The compression's scratch serves as a block
-  // where it is of the size of the panels and, beside the factors, within that
-  // bound.
+  // Blocks for the arrays.  The compression's scratch serves as one where it
+  // is of the size of the panels and, beside the far factors, no more than the
+  // finished handle.
   const DataBytes need = data_bytes(h);
   const int64_t panels = need.packed + need.rest;
   const bool adopted = dev && fs->ws.p && fs->ws_bytes <= panels &&
@@ -2902,7 +2907,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       (void)hipFree(fs->ws.p);
       fs->ws.p = nullptr;
     }
-    reserve_data(h, need.packed);
+    reserve_data(h, need.two_blocks() ? need.packed : panels);
   }
   // U (fb.m x r) and V (fb.n x r) of far block b's orientation on the device
   auto dev_u = [&](int b) -> const double2* {
@@ -3265,7 +3270,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   STCHK(upload(h, &h->ir_row0, ir_row0, st));
   STCHK(upload(h, &h->ir_soff, ir_soff, st));
   STCHK(upload(h, &h->ir_n, ir_n, st));
-  if (!adopted) reserve_data(h, need.rest);
+  if (!adopted && need.two_blocks()) reserve_data(h, need.rest);
   STCHK(dalloc(h, (void**)&h->Dinv, sizeof(double2) * std::max<int64_t>(ditot, 1) + kPanelPad));
   HIPCHK(hipMemsetAsync(h->Dinv, 0, sizeof(double2) * std::max<int64_t>(ditot, 1) + kPanelPad, st));
   STCHK(dalloc(h, (void**)&h->piv, sizeof(int32_t) * ptot));
@@ -4332,13 +4337,14 @@ int park_factors(hm_matrix_t h) {
 }
 
 // Device bytes the device part of the build will allocate (its blocks, the
-// sources, and up to 512 KB of small arrays that fit no tail), plus the
-// workspace for nrhs right-hand sides.  Spheres and cubes of 300 to 24,576
-// points, 1 to 64 right-hand sides: from 0.999 to 1.05 of what is allocated.
+// sources, and up to 1 MB of arrays that fit no tail), plus the workspace for
+// nrhs right-hand sides.  Spheres and cubes of 300 to 24,576 points, 1 to 64
+// right-hand sides: from 0.998 to 1.05 of what is allocated.
 int64_t device_bytes_estimate(hm_matrix_t h, int nrhs) {
   const DataBytes d = data_bytes(h);
-  const int64_t blocks = block_bytes(d.packed) + block_bytes(d.rest) + block_bytes(d.half);
-  return blocks + std::min<int64_t>(blocks / 100, (int64_t)512 << 10) + d.sources +
+  const int64_t panels = d.two_blocks() ? block_bytes(d.packed) + block_bytes(d.rest) : block_bytes(d.packed + d.rest);
+  const int64_t blocks = panels + block_bytes(d.half);
+  return blocks + std::min<int64_t>(blocks / 64, (int64_t)1 << 20) + d.sources +
          workspace_bytes(h, nrhs, d.T);
 }
 
