@@ -212,11 +212,10 @@ struct MMAcc {
 // for the RTL row tiles r < RTL of this wave.  P is column-major with
 // leading dimension ld (its allocation extends at least 16 rows past the
 // last column, so the row tiles need no clamp: rows past ld read the next
-// column, and rows past m are never stored); srcf(c) is the X row holding
-// column c's input, and a row of zeros for columns from c1 on (up to
-// 4 (D + 1) past it).  D k-steps of four columns are in flight: the panel
-// loads of the first D start before `ready` is called, which makes srcf
-// usable (it may hold a workgroup barrier).  Panel loads past c1 are issued
+// column, and rows past m are never stored); srcf(c), c < c1, is the X row
+// holding column c's input (columns past c1 take the row of zeros).  D k-steps
+// of four columns are in flight: the panel loads of the first D start before
+// `ready` is called, which makes srcf usable (it may hold a workgroup barrier).  Panel loads past c1 are issued
 // at the clamped column c1 - 1; right-hand sides past the row length are
 // read at the clamped column ldr - 1 (their products land in result columns
 // that are never stored).  CO: the inputs are read with device-coherent
@@ -295,10 +294,9 @@ __device__ __forceinline__ void mm_wave(const void* __restrict__ P, uint32_t ld,
 template <int RT, int NT, int WR>
 struct MMShared {
   static constexpr int WK = 4 / WR;
-  static constexpr int kPadCols = 128;  // zero-row sources past the piece
   static constexpr int kZld = 16 * RT * WR + 1;
   union {
-    int src[kMmMaxCols + kPadCols];
+    int src[kMmMaxCols];
     double2 red[WK > 1 ? WR * WK * (WK - 1) * 256 : 1];
     double2 z[16 * kZld];
   };
@@ -426,19 +424,17 @@ __device__ __forceinline__ void sum_pieces(const TermArgs& A, int m, int np, int
   }
 }
 
-// The products of one wave over columns [c0, c1) for its rtl row tiles,
-// the tile count a template argument from RT down to LO (a leaf with fewer
-// tiles runs LO of them: rows past m read later columns or the pad, and are
-// never stored).
-template <int PM, int RT, int NT, int RTL, int LO, bool CO, typename SRCF, typename READY>
+// The products of one wave over columns [c0, c1) for its rtl row tiles (at
+// least one), the tile count a template argument from RT down.
+template <int PM, int RT, int NT, int RTL, bool CO, typename SRCF, typename READY>
 __device__ __forceinline__ void mm_wave_tiles(int rtl, const void* P, uint32_t ld, int row0, int c0,
                                               int c1, const SRCF& srcf, const READY& ready,
                                               const typename Prec<PM>::X* xr, int64_t ldr, int zrow,
                                               int rhs0, MMAcc<PM, RT, NT>& acc, int lane) {
-  if constexpr (RTL > LO) {
+  if constexpr (RTL > 1) {
     if (rtl < RTL) {
-      mm_wave_tiles<PM, RT, NT, RTL - 1, LO, CO>(rtl, P, ld, row0, c0, c1, srcf, ready, xr, ldr, zrow,
-                                                  rhs0, acc, lane);
+      mm_wave_tiles<PM, RT, NT, RTL - 1, CO>(rtl, P, ld, row0, c0, c1, srcf, ready, xr, ldr, zrow,
+                                             rhs0, acc, lane);
       return;
     }
   }
@@ -491,21 +487,20 @@ __device__ __forceinline__ bool term_piece(const TermArgs& A, const MMPiece* __r
   // every source of the piece in one pass, then the barrier
   auto ready = [&] {
     const int n = pc1 - pc0;
-    for (int c = threadIdx.x; c < n + MMShared<RT, NT, WR>::kPadCols; c += kThreads)
-      sh.src[c] = c < n ? src[pc0 + c] : A.zrow;
+    for (int c = threadIdx.x; c < n; c += kThreads) sh.src[c] = src[pc0 + c];
     __syncthreads();
   };
   auto srcf = [&](int c) -> int { return sh.src[c - pc0]; };
   if (rtl > 0 && c1 > c0)
-    mm_wave_tiles<PM, RT, NT, RT, (RT > 4 ? 4 : 1), MT>(rtl, P, ld, row0, c0, c1, srcf, ready, xr,
-                                                         A.ldr, A.zrow, rhs0, acc, lane);
+    mm_wave_tiles<PM, RT, NT, RT, MT>(rtl, P, ld, row0, c0, c1, srcf, ready, xr, A.ldr, A.zrow, rhs0,
+                                      acc, lane);
   else
     ready();
   const int l16 = lane & 15, kq = lane >> 4;
   const __amdgpu_buffer_rsrc_t rs =
       uniform_rsrc(A.partial + prow * A.ldr, (uint32_t)m * (uint32_t)A.ldr * 16u);
   // row tiles the products ran with (the paired ones hold even and odd rows)
-  const int tiles = max(rtl, RT > 4 ? 4 : 1);
+  const int tiles = max(rtl, 1);
   // element v of tile (r, t): the leaf's z (its only piece), or the piece's
   // partial row
   constexpr int kZld = MMShared<RT, NT, WR>::kZld;
@@ -610,8 +605,7 @@ __device__ __forceinline__ bool term_piece(const TermArgs& A, const MMPiece* __r
 // memory by one XCD at about one time; the plain order when the unit count
 // is not a multiple of 8.
 template <int PM, int RT, int NT, int WR>
-__global__ __launch_bounds__(kThreads, 2) void k_term_mm(TermArgs A, int nrhs,
-                                                                              int nunits, int ntiles) {
+__global__ __launch_bounds__(kThreads, 2) void k_term_mm(TermArgs A, int nrhs, int nunits, int ntiles) {
   __shared__ MMShared<RT, NT, WR> sh;
   const int lane = threadIdx.x & 63;
   const int w = wave_id();
