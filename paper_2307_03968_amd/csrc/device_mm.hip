@@ -595,15 +595,15 @@ __device__ __forceinline__ bool term_piece(const TermArgs& A, const MMPiece* __r
 
 // Term kernel: a workgroup runs the pieces of one unit for one tile of
 // right-hand sides.  Bound by the matrix cores with 64 right-hand sides, by
-// the panel reads with 16.  One wave per piece with up to 64 partial rows a
-// leaf, which a single wave added up, took 2,047 us a term on the sphere of
-// 6,000 points (64 RHS, FP32) where this split takes 62; 16 to 64 instances
-// of 16 RHS: FP64 466 and FP32 625 us, now 300 to 340 and 547.  Workgroups are dispatched to the eight XCDs in turn
-// (workgroup b to XCD b mod 8), each XCD with its own L2.  XCD x runs a
-// contiguous range of the units (their leaves read overlapping input rows),
-// the tiles of one unit one after another, so that a panel is read from
-// memory by one XCD at about one time; the plain order when the unit count
-// is not a multiple of 8.
+// the panel reads with 16.  One wave per piece, and one wave to add up to 64
+// partial rows a leaf, took 2,047 us a term on the sphere of 6,000 points (64
+// RHS, FP32) where this split takes 62; with 16 RHS, FP64 on 16 instances 466
+// us (now 300 to 340), FP32 on 64 instances 625 (now 547).
+// Workgroups are dispatched to the eight XCDs in turn (workgroup b to XCD
+// b mod 8), each XCD with its own L2.  XCD x runs a contiguous range of the
+// units (their leaves read overlapping input rows), the tiles of one unit one
+// after another, so that a panel is read from memory by one XCD at about one
+// time; the plain order when the unit count is not a multiple of 8.
 template <int PM, int RT, int NT, int WR>
 __global__ __launch_bounds__(kThreads, 2) void k_term_mm(TermArgs A, int nrhs, int nunits, int ntiles) {
   __shared__ MMShared<RT, NT, WR> sh;

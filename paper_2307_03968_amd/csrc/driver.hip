@@ -65,9 +65,9 @@ struct GroupList {
 }  // namespace hm
 
 // Device memory of one owner, freed together.  A handle's arrays are cut from
-// few blocks (reserve, adopt): freeing a block of more than 64 MB takes 0.3 ms
-// whatever its size (a 5,800-point handle: 7.1 ms to release in a block per
-// array, 1.5 ms so).
+// few blocks (reserve, adopt): the driver takes about 0.25 ms for every 64 MB
+// or so it is given back in small blocks, and as much for a larger block whole
+// (a 5,800-point handle: 7.1 ms to release in a block per array, 1.5 ms so).
 struct Slabs {
   struct Tail { char* cur; size_t left; };
   std::vector<void*> blocks;
@@ -441,9 +441,13 @@ struct MMPanels {
 // 222 us a solve, two 250); two per CU, a resident round, from 48 M entries on
 // (sphere 24,576, 57 M, 16 RHS, FP64: 913 against 968), 64 M with small
 // leaves; for those eight from 200 M and sixteen from 800 M, so that the
-// dispatcher evens out units that take unequal time (64 instances, 247 M,
-// FP32: 547 us a term against 630 with two).  D^{-1} lists are small: a unit of 2,048 entries (a leaf of
-// 47 rows by itself; 16,384 took 84 us against 10 on 128 leaves).
+// dispatcher evens out units that take unequal time (four terms, 16 RHS, FP32
+// / FP64: 48 instances, 197 M, 2,373 / 4,267 us with two and 2,270 / 4,024 with
+// eight, 64 instances, 267 M, 3,234 / 5,915 and 3,019 / 5,431; 192 instances,
+// 702 M, 8,205 / 14,664 with eight and 8,014 / 14,435 with sixteen, 224
+// instances, 823 M, 8,926 / 15,481 and 8,492 / 15,081).  D^{-1} lists are small:
+// a unit of 2,048 entries (a leaf of 47 rows by itself; 16,384 took 84 us
+// against 10 on 128 leaves).
 int64_t mm_two_per_cu(const hm_matrix* h) { return mm_small_leaf(h->max_m) ? 64000000 : 48000000; }
 int mm_units(const hm_matrix* h, int64_t total, bool dinv) {
   const int64_t cus = h->num_cus;
@@ -802,11 +806,10 @@ int upload_groups(hm_matrix* h, const std::vector<GroupItem>& v, GroupList& gl, 
   return upload(h, &gl.items, v, st);
 }
 
-// Split-K counters: per (leaf, right-hand-side tile) for the streaming
-// kernels, per (leaf, block of rows < 4, 16-RHS tile) for the matrix cores.
-int64_t counter_count(const hm_matrix* h, int nrhs) {
-  return (int64_t)h->nl * std::max<int64_t>(nrhs, 4 * ((nrhs + 15) / 16));
-}
+// Split-K counters: every kernel takes one per leaf and tile of right-hand
+// sides (1, 2 or 4; 16, 32 or 64 on the matrix cores), at most one per
+// right-hand side.
+int64_t counter_count(const hm_matrix* h, int nrhs) { return (int64_t)h->nl * nrhs; }
 
 // Entries of the partial-sum buffer for nrhs right-hand sides: column layout
 // (streaming and, for one right-hand side, half-storage kernels) or row layout
@@ -4339,7 +4342,7 @@ int park_factors(hm_matrix_t h) {
 // Device bytes the device part of the build will allocate (its blocks, the
 // sources, and up to 1 MB of arrays that fit no tail), plus the workspace for
 // nrhs right-hand sides.  Spheres and cubes of 300 to 24,576 points, 1 to 64
-// right-hand sides: from 0.998 to 1.05 of what is allocated.
+// right-hand sides: from 0.993 to 1.05 of what is allocated.
 int64_t device_bytes_estimate(hm_matrix_t h, int nrhs) {
   const DataBytes d = data_bytes(h);
   const int64_t panels = d.two_blocks() ? block_bytes(d.packed) + block_bytes(d.rest) : block_bytes(d.packed + d.rest);
