@@ -83,18 +83,19 @@ struct Slabs {
     tails.clear();
     bytes = 0;
   }
-  // Room for the next arrays, `bytes` in all, with what is left of earlier
-  // blocks; without memory for it, and where an array fits no tail, it gets a
-  // block of its own.
-  void reserve(size_t size) {
+  // Room for the next arrays, `size` bytes in all, with what is left of earlier
+  // blocks.  Without memory for it (false), and where an array fits no tail, an
+  // array gets a block of its own.
+  bool reserve(size_t size) {
     for (const Tail& t : tails) size -= std::min(size, t.left);
     void* b = nullptr;
-    if (size == 0) return;
+    if (size == 0) return true;
     if (hipMalloc(&b, size) != hipSuccess) {
       (void)hipGetLastError();
-      return;
+      return false;
     }
     adopt(b, size);
+    return true;
   }
   // A block that served something else, for the next arrays (not zeroed).
   void adopt(void* b, size_t size) {
@@ -2062,13 +2063,9 @@ int build_lists(hm_matrix* h, hipStream_t st) {
 // until they are packed; the sources of the panel columns; T: far coefficients.
 struct DataBytes {
   int64_t packed, rest, half, far, sources, T;
-  // The rest of the panels gets its block once the factors are gone where the
-  // half storage would not take their room later anyway, so that a build never
-  // holds more than the handle it ends with.  One block for all panels
-  // otherwise: the driver takes 0.25 ms for every 64 MB or so it is given back
-  // and as much for a larger block whole (1,500 points: build, solve and release
-  // 4.3 ms with two blocks, 3.9 with one).
-  bool two_blocks() const { return far > half; }
+  // Whether the far factors beside all panels are more than the finished
+  // handle (the half storage would not take their room later).
+  bool beyond() const { return far > half; }
 };
 DataBytes data_bytes(const hm_matrix* h) {
   const HostH& H = h->H;
@@ -2110,8 +2107,8 @@ DataBytes data_bytes(const hm_matrix* h) {
 int64_t block_bytes(int64_t bytes) {
   return bytes > 0 ? bytes + bytes / 100 + std::min<int64_t>(bytes / 16, (int64_t)1 << 20) : 0;
 }
-void reserve_data(hm_matrix* h, int64_t bytes) {
-  if (bytes > 0) h->mem.reserve((size_t)block_bytes(bytes));
+bool reserve_data(hm_matrix* h, int64_t bytes) {
+  return bytes <= 0 || h->mem.reserve((size_t)block_bytes(bytes));
 }
 
 // Host layout of the far-field device arrays the half-storage data is
@@ -2213,9 +2210,10 @@ struct FarStore {
     }
     return HM_OK;
   }
-  // the scratch of the compression, for the handle's arrays (keep_ws): the
-  // driver stalls for up to seconds where blocks are freed and allocated at
-  // more than some 80 GB/s, which builds in a row do without this
+  // A build on its own, not a server's, whose memory is counted: it keeps the
+  // scratch of the compression for the handle's arrays (the driver stalls for
+  // up to seconds where blocks are freed and allocated at more than some 80
+  // GB/s, which builds in a row do without this).
   bool keep_ws = false;
   DevTmp<double2> ws;
   int64_t ws_bytes = 0;
@@ -2896,12 +2894,18 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   }
   // Blocks for the arrays.  The compression's scratch serves as one where it
   // is of the size of the panels and, beside the far factors, no more than the
-  // finished handle.
+  // finished handle.  Else one block for all panels: the driver takes 0.25 ms
+  // for every 64 MB or so it is given back and as much for a larger block whole
+  // (1,500 points: build, solve and release 4.3 ms with two blocks, 3.9 with
+  // one).  Where the factors beside it are more than the finished handle, and
+  // memory is counted (a server's build) or short, the rest of the panels gets
+  // its block once the factors are gone, so that what fits is built.
   const DataBytes need = data_bytes(h);
   const int64_t panels = need.packed + need.rest;
   const bool adopted = dev && fs->ws.p && fs->ws_bytes <= panels &&
                        fs->ws_bytes >= panels / 2 &&
                        fs->ws_bytes + fs->bytes() <= panels + need.half;
+  bool two_blocks = dev && need.beyond() && !fs->keep_ws;
   if (adopted) {
     h->mem.adopt(fs->ws.p, (size_t)fs->ws_bytes);
     fs->ws.p = nullptr;
@@ -2910,7 +2914,10 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
       (void)hipFree(fs->ws.p);
       fs->ws.p = nullptr;
     }
-    reserve_data(h, need.two_blocks() ? need.packed : panels);
+    if (two_blocks || !reserve_data(h, panels)) {
+      two_blocks = true;
+      reserve_data(h, need.packed);
+    }
   }
   // U (fb.m x r) and V (fb.n x r) of far block b's orientation on the device
   auto dev_u = [&](int b) -> const double2* {
@@ -3273,7 +3280,7 @@ int build_device(hm_matrix* h, const hm_build_opts* opts, hipStream_t st) {
   STCHK(upload(h, &h->ir_row0, ir_row0, st));
   STCHK(upload(h, &h->ir_soff, ir_soff, st));
   STCHK(upload(h, &h->ir_n, ir_n, st));
-  if (!adopted && need.two_blocks()) reserve_data(h, need.rest);
+  if (!adopted && two_blocks) reserve_data(h, need.rest);
   STCHK(dalloc(h, (void**)&h->Dinv, sizeof(double2) * std::max<int64_t>(ditot, 1) + kPanelPad));
   HIPCHK(hipMemsetAsync(h->Dinv, 0, sizeof(double2) * std::max<int64_t>(ditot, 1) + kPanelPad, st));
   STCHK(dalloc(h, (void**)&h->piv, sizeof(int32_t) * ptot));
@@ -4345,7 +4352,7 @@ int park_factors(hm_matrix_t h) {
 // right-hand sides: from 0.993 to 1.05 of what is allocated.
 int64_t device_bytes_estimate(hm_matrix_t h, int nrhs) {
   const DataBytes d = data_bytes(h);
-  const int64_t panels = d.two_blocks() ? block_bytes(d.packed) + block_bytes(d.rest) : block_bytes(d.packed + d.rest);
+  const int64_t panels = d.beyond() ? block_bytes(d.packed) + block_bytes(d.rest) : block_bytes(d.packed + d.rest);
   const int64_t blocks = panels + block_bytes(d.half);
   return blocks + std::min<int64_t>(blocks / 64, (int64_t)1 << 20) + d.sources +
          workspace_bytes(h, nrhs, d.T);

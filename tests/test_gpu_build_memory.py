@@ -56,6 +56,27 @@ def test_build_peak_is_the_handle(make, leaf, tol, flags):
     h.close()
 
 
+@pytest.mark.parametrize("flags", [0, hmps.HM_BUILD_NO_HALF], ids=["half", "no_half"])
+def test_build_that_just_fits(flags):
+    """With memory for the finished handle and half the far factors, the handle
+    is built, with the same result."""
+    prob = W.sphere_problem(24576, 4.0)
+    b = torch.from_numpy(np.ascontiguousarray(W.plane_waves(prob.xyz, W.Z_HAT).reshape(-1))).to("cuda")
+    base = _used()
+    h = hmps.HMatrix(prob, 128, 1.0, 1e-4, flags=flags)
+    end, far = _used() - base, _far_bytes(h.info())
+    x = h.solve(b, K=2).cpu().numpy()
+    h.close()
+    free, _ = torch.cuda.mem_get_info()
+    fill = torch.empty(free - end - far // 2, dtype=torch.uint8, device="cuda")
+    print(f"[gpu-case] build of {end / MB:.0f} MB in {torch.cuda.mem_get_info()[0] / MB:.0f} MB, flags={flags}", flush=True)
+    h = hmps.HMatrix(prob, 128, 1.0, 1e-4, flags=flags)
+    del fill
+    torch.cuda.empty_cache()
+    assert np.array_equal(h.solve(b, K=2).cpu().numpy(), x)
+    h.close()
+
+
 def test_server_resident_bytes_are_what_the_device_gave_out():
     """Workspace and GMRES basis (32 right-hand sides: 96 and 192 MB) included."""
     srv = hmps.Server(slots=1)
