@@ -4416,6 +4416,17 @@ int64_t gmres_growth_bytes(hm_matrix_t h, int m, int nrhs) {
 
 int gmres_rhs(hm_matrix_t h, int m) { return m <= h->gm_m ? h->gm_nrhs : 0; }
 
+bool gmres_held(hm_matrix_t h) { return h->gm_mem.bytes > 0; }
+
+int64_t release_gmres(hm_matrix_t h, std::vector<void*>& blocks) {
+  const int64_t bytes = h->gm_mem.bytes;
+  blocks.insert(blocks.end(), h->gm_mem.blocks.begin(), h->gm_mem.blocks.end());
+  h->gm_mem.blocks.clear();
+  h->gm_mem.clear();
+  h->gm_m = h->gm_nrhs = 0;
+  return bytes;
+}
+
 int64_t resident_bytes(hm_matrix_t h) {
   return h->mem.bytes + h->list_mem.bytes + h->ws_mem.bytes + h->gm_mem.bytes;
 }

@@ -211,6 +211,10 @@ constexpr int kMmMinRhsF64 = 5;      // the same for FP64 blocks when the thresh
 int gmres_restart(const ps_opts& o);
 int64_t gmres_growth_bytes(hm_matrix_t h, int m, int nrhs);
 int gmres_rhs(hm_matrix_t h, int m);   // right-hand sides the GMRES basis holds at restart m
+bool gmres_held(hm_matrix_t h);        // whether the handle keeps a basis
+// the basis leaves the handle, which no call may be using: its blocks join
+// `blocks`, for the caller to free; returns their bytes
+int64_t release_gmres(hm_matrix_t h, std::vector<void*>& blocks);
 int64_t matrix_n(hm_matrix_t h);
 
 // Export helper (binary named arrays).

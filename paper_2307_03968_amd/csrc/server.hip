@@ -26,8 +26,10 @@
 // the oldest goes on and the others give their geometries up to it (their
 // requests return to the queue), as it does itself where only queued requests
 // of other resident geometries are in its way.  So some batch always goes on.
-// Handles freed to make room are released after the server lock is
-// dropped (a free synchronises the device).
+// GMRES bases of geometries without a worker go before any geometry does: they
+// are made again by a call, a geometry by a build.
+// What is freed to make room is released after the server lock is dropped (a
+// free synchronises the device).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -89,6 +91,19 @@ struct Request {
   bool cold = false;  // its batch had to build the geometry
 };
 
+// Handles and GMRES bases that gave way, released without the server's lock.
+struct Freed {
+  std::vector<hm_matrix_t> handles;
+  std::vector<void*> blocks;
+  bool empty() const { return handles.empty() && blocks.empty(); }
+  void release() {
+    for (hm_matrix_t h : handles) hmat_free(h);
+    for (void* b : blocks) (void)hipFree(b);
+    handles.clear();
+    blocks.clear();
+  }
+};
+
 bool same_opts(const ps_opts& a, const ps_opts& b) {
   return a.K == b.K && a.level == b.level && a.precision == b.precision && a.kind == b.kind &&
          a.max_passes == b.max_passes && a.refine_tol == b.refine_tol &&
@@ -118,9 +133,10 @@ struct hm_server {
     return r;
   }
   void worker(int slot);
-  // with mu held: drop idle geometries (LRU first) until need more bytes
-  // fit; their handles go to `freed`, to be released without the lock
-  bool make_room(int64_t need, uint64_t except, std::vector<hm_matrix_t>& freed);
+  // with mu held: drop the GMRES bases of geometries without a worker, then
+  // geometries without requests (LRU first) until need more bytes fit; what
+  // goes is in `freed`, to be released without the lock
+  bool make_room(int64_t need, uint64_t except, Freed& freed);
   // with mu held: a resident geometry other than `except` with queued
   // requests and no worker on it
   bool runnable_elsewhere(uint64_t except) const {
@@ -144,36 +160,38 @@ struct hm_server {
   // geometry holds workspace for a narrower piece already.
   enum Room { kRoom, kNoRoom, kGiveUp };
   Room wait_room(int64_t extra, uint64_t key, hm_ticket_t id, bool chunked,
-                 std::vector<hm_matrix_t>& freed, std::unique_lock<std::mutex>& lk);
+                 Freed& freed, std::unique_lock<std::mutex>& lk);
   void finish(std::vector<Request*>& batch, int status, const std::string& err);
 };
 
-bool hm_server::make_room(int64_t need, uint64_t except, std::vector<hm_matrix_t>& freed) {
-  while (resident() + need > budget) {
-    uint64_t victim = 0;
-    bool found = false;
-    clk::time_point oldest = clk::time_point::max();
+bool hm_server::make_room(int64_t need, uint64_t except, Freed& freed) {
+  // least recently used geometry without a worker that `ok` takes
+  auto victim = [&](auto ok) -> Geometry* {
+    Geometry* v = nullptr;
     for (auto& kv : geoms) {
-      const Geometry& g = kv.second;
-      if (kv.first == except || !g.h || g.busy || g.building || g.pending > 0) continue;
-      if (g.last_used < oldest) {
-        oldest = g.last_used;
-        victim = kv.first;
-        found = true;
-      }
+      Geometry& g = kv.second;
+      if (kv.first == except || !g.h || g.busy || g.building || !ok(g)) continue;
+      if (!v || g.last_used < v->last_used) v = &g;
     }
-    if (!found) return false;
-    Geometry& g = geoms[victim];
-    freed.push_back(g.h);
-    g.h = nullptr;
-    g.bytes = 0;
+    return v;
+  };
+  while (resident() + need > budget) {
+    if (Geometry* g = victim([](const Geometry& g) { return hm::gmres_held(g.h); })) {
+      g->bytes -= hm::release_gmres(g->h, freed.blocks);
+      continue;
+    }
+    Geometry* g = victim([](const Geometry& g) { return g.pending == 0; });
+    if (!g) return false;
+    freed.handles.push_back(g->h);
+    g->h = nullptr;
+    g->bytes = 0;
     st.evictions++;
   }
   return true;
 }
 
 hm_server::Room hm_server::wait_room(int64_t extra, uint64_t key, hm_ticket_t id, bool chunked,
-                                     std::vector<hm_matrix_t>& freed,
+                                     Freed& freed,
                                      std::unique_lock<std::mutex>& lk) {
   Geometry& g = geoms[key];
   Room r = kRoom;
@@ -207,10 +225,8 @@ hm_server::Room hm_server::wait_room(int64_t extra, uint64_t key, hm_ticket_t id
     g.waiting = id;
     if (tell) cv.notify_all();
     if (!freed.empty()) {  // what was evicted so far is released, not held
-      std::vector<hm_matrix_t> gone;
-      gone.swap(freed);
       lk.unlock();
-      for (hm_matrix_t f : gone) hmat_free(f);
+      freed.release();
       lk.lock();
       continue;
     }
@@ -317,7 +333,7 @@ void hm_server::worker(int slot) {
       }
       const int64_t need = s == HM_OK ? hm::device_bytes_estimate(h, head->nrhs) : 0;
       lk.lock();
-      std::vector<hm_matrix_t> freed;
+      Freed freed;
       bool aside = false, parked = false;
       while (s == HM_OK && !make_room(need, key, freed)) {
         // a build without its room holds no device memory
@@ -350,7 +366,7 @@ void hm_server::worker(int slot) {
         g.wait_room = true;
         g.building = false;
         lk.unlock();
-        for (hm_matrix_t f : freed) hmat_free(f);
+        freed.release();
         lk.lock();
         cv.notify_all();
         continue;
@@ -360,8 +376,7 @@ void hm_server::worker(int slot) {
         g.bytes = need;  // reserved until the real size is known
         g.reserved = true;
         lk.unlock();
-        for (hm_matrix_t f : freed) hmat_free(f);
-        freed.clear();
+        freed.release();
         s = hm::build_device_phase(h, &spec->opts, stream);
         if (s == HM_OK && hipStreamSynchronize(stream) != hipSuccess) s = HM_EHIP;
         if (s != HM_OK) err = hm_last_error();
@@ -371,8 +386,7 @@ void hm_server::worker(int slot) {
       g.reserved = false;
       if (!freed.empty()) {
         lk.unlock();
-        for (hm_matrix_t f : freed) hmat_free(f);
-        freed.clear();
+        freed.release();
         lk.lock();
       }
       if (s != HM_OK) {
@@ -425,7 +439,7 @@ void hm_server::worker(int slot) {
     // in pieces of the width the geometry's workspace already holds.
     int s = HM_OK;
     std::string err;
-    std::vector<hm_matrix_t> freed;
+    Freed freed;
     int chunk = cols;
     Room room = kRoom;
     if (cols > hm::workspace_rhs(h)) {
@@ -463,13 +477,13 @@ void hm_server::worker(int slot) {
         auto at = std::find_if(queue.begin(), queue.end(), [&](Request* q) { return q->id > (*r)->id; });
         queue.insert(at, *r);
       }
-      freed.push_back(h);
+      freed.handles.push_back(h);
       g.h = nullptr;
       g.bytes = 0;
       g.busy = false;
       st.evictions++;
       lk.unlock();
-      for (hm_matrix_t f : freed) hmat_free(f);
+      freed.release();
       lk.lock();
       cv.notify_all();
       continue;
@@ -478,7 +492,7 @@ void hm_server::worker(int slot) {
     st.batch_rhs += cols;
     if (chunk < cols) st.split_batches++;
     lk.unlock();
-    for (hm_matrix_t f : freed) hmat_free(f);
+    freed.release();
 
     // ---- run: pack b, copy in, solve, copy out
     if (s == HM_OK) {

@@ -68,3 +68,31 @@ def test_two_batches_wait_for_room(gmres):
         assert info["builds"] >= 4  # one was given up and built again
     else:
         assert info["split_batches"] >= 1
+
+
+def test_gmres_bases_give_way_before_geometries():
+    """Room for a wider workspace comes from the GMRES basis that another, idle
+    geometry keeps; the geometry stays, and its next GMRES batch is right."""
+    gm = dict(K=4, kind=hmps.PS_GMRES, max_passes=200, refine_tol=1e-8)
+
+    def warm(srv):
+        for key in (1, 2):
+            srv.wait(srv.submit(key, _b(key, 16, key), K=2, prob=PROBS[key], leaf_max=64))
+        return srv.wait(srv.submit(1, _b(1, 16, 5), **gm))[0]
+
+    srv = hmps.Server(slots=1)
+    warm(srv)
+    budget = srv.info()["resident_bytes"] + 24 * MB
+    srv.close()
+    srv = hmps.Server(budget_bytes=budget, slots=1)
+    want = warm(srv)
+    before = srv.info()
+    print(f"[gpu-case] GMRES bases give way, {before}", flush=True)
+    srv.wait(srv.submit(2, _b(2, 24, 6), K=3))
+    after = srv.info()
+    assert before["evictions"] == after["evictions"] == 0 and after["split_batches"] == 0
+    assert after["resident_bytes"] <= budget
+    x, st = srv.wait(srv.submit(1, _b(1, 16, 5), **gm))
+    assert_close(x, want, 1e-6)
+    assert all(s["diverged"] == 0 for s in st)
+    srv.close()
