@@ -2,7 +2,7 @@
 // partial pivoting, then recompression by QR of both factors and an SVD of
 // the small core.  Host code.
 //
-// Rules (shared with the independent FP64 checker so both produce the same
+// Rules (shared with the FP64 oracle so both produce the same
 // approximant up to rounding):
 //   ACA on A (m x n), tolerance eps, rank cap r_max:
 //     start at row 0; residual row = A[i,:] - sum_k u_k[i] v_k;
