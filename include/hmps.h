@@ -311,8 +311,10 @@ int hmat_export(hm_matrix_t h, const char* path);
  * on the matrix cores a count that follows the size of the list).
  * Results do not depend on these values beyond rounding order.  Changing
  * term_wgs or inrow_pct rebuilds the work lists (synchronises the stream); the handle
- * must not be in use on another stream meanwhile.  In hmat_tune a field of
- * 0 keeps its value and -1 restores the default. */
+ * must not be in use on another stream meanwhile; when a rebuild fails, solves
+ * and products on the handle return HM_ESTATE until a later hmat_tune builds the
+ * lists.  In hmat_tune a field of 0 keeps its value and -1 restores the
+ * default. */
 typedef struct {
   int32_t mm_min_rhs;
   int32_t term_wgs;
